@@ -542,6 +542,7 @@ __global__ void k_apply_keep(int64_t ns, int prec, const uint8_t *__restrict__ k
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 __device__ double g_zero_word[2];   // zero-initialised source of padding (16 bytes)
+__device__ __align__(256) double g_zero_page[32];   // zeros for a whole column of an absent tile (kMaxFun rows)
 
 struct GroupArgs {
     const int32_t *grp_mem, *grp_s, *grp_g;
@@ -574,6 +575,35 @@ struct KTab {
                           // tile in some middle cluster of the stage (grouped kernel only)
     int32_t pad[2];
 };
+
+// Stage records of the register-direct FP64 and FP32 kernels: for every member slot (as in
+// KTab) and k row the address of the member's column of the operand, or of a page of zeros
+// where the tile is absent or the row is padding, so that a consumer lane adds its row and
+// loads, with one vector instruction and no select.  That matters because a v_mfma_f64
+// keeps the SIMD's vector unit to itself for its 64 cycles (measured: integer instructions
+// of another wave make no progress meanwhile), so the product's time is the sum of both.
+// Slots are 36 entries apart: the writer's lanes are then consecutive in LDS, and the
+// readers' four k rows of four members fall into different banks.
+struct ATab {
+    uint64_t adr[8][kKS + 4];
+    int32_t ks;           // k rows of the stage (its clusters packed without padding)
+    int32_t act;          // bit q: member slot q has a tile in some middle cluster of the stage
+    int32_t act_half[2];  // the same for each half of 16 k rows
+};
+
+// An LDS address that is the same in every lane, as a scalar (the destination of a direct
+// load to LDS is one; the compiler loops over the lanes of one it cannot tell is uniform).
+__device__ inline double *uniform_lds(double *p)
+{
+    const uint32_t o = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double *)p;
+    return (double *)(__attribute__((address_space(3))) double *)(uintptr_t)__builtin_amdgcn_readfirstlane(o);
+}
+
+template <typename T>
+__device__ inline T load_at(uint64_t adr, int64_t i)
+{
+    return ((const __attribute__((address_space(1))) T *)adr)[i];
+}
 
 template <int WAVES>
 __device__ inline void unit_sync()
@@ -1026,34 +1056,42 @@ struct OzTab {
     int32_t pad[2];
 };
 
-template <int LEAD, typename Rec = KTab>
+template <int LEAD, typename Rec = ATab>
 constexpr size_t ring_bytes()
 {
     return (((LEAD + 1) * sizeof(Rec) + 15) & ~(size_t)15) + 4 * (128 * 8 + 3 * 64 * 4);
 }
 
 // The fragment that every consumer wave of a unit needs (the unit's single 16-row side),
-// which the record wave copies into LDS once instead: per stage four quarters of 64 lanes
-// x 16 bytes, lane L holding what consumer lane L would load itself (the rows 2m, 2m + 1
-// of one k column, at k step 2q for even and 2q + 1 for odd lanes).  The copy of stage t
-// goes into slot t of a ring of as many slots as the record ring.
+// which the record wave copies into LDS once instead, 512 doubles per stage.  FP64: the
+// k-major panel [32 k rows][16 rows], copied eight k rows at a time, lane L the row pair
+// L % 8 of k row L / 8.  Split precision: four quarters of 64 lanes x 16 bytes, lane L
+// what consumer lane L would load itself.  The copy of stage t goes into slot t of a ring
+// of as many slots as the record ring.
 struct SharedSide {
-    const double *X;     // operand of the shared side
+    const double *X;     // operand of the shared side (split precision)
     double *dst;         // LDS ring, 512 doubles per slot
     int slot;            // record column of the lane's member
-    int ipair;           // offset of the lane's row pair inside a tile column (split-precision
-                         // records: the lane's row inside its member)
-    int kodd;            // 1 on odd lanes
-    bool ok;             // the lane's row exists
+    int row;             // FP64: byte offset of the lane's rows in a column of its member;
+                         // split precision: the lane's row inside its member
+    bool ok;             // the lane's row exists (split precision)
 };
 
-template <int LEAD, bool SHARE, typename Rec = KTab>
+// s_waitcnt operand that waits for all but the newest n vector memory operations
+constexpr int vmcnt_at_most(int n) { return (n & 15) | (n >> 4) << 14 | 0x70 | 0xF00; }
+
+// A and B: the operands' addresses, ES bytes per value (ATab records; unused for OzTab).
+// CW: bytes per lane of the copies of the shared side (4 when a cluster size is odd).
+template <int LEAD, bool SHARE, int ES, typename Rec = ATab, int CW = 16>
 __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *lds, Rec *ring, int lane,
-                                const SharedSide &sh)
+                                const SharedSide &sh, const void *A, const void *B)
 {
     // OzTab records: g.gl_offd holds the offsets of the transposed tiles (mu, member) and
     // g.gl_nm the cluster size | level << 8 (the caller passes those tables)
     constexpr bool OZ = std::is_same<Rec, OzTab>::value;
+    // ahead of the consumer waves of its SIMD: every vector instruction would else wait for
+    // their MFMAs, which hold the vector unit for 64 cycles each
+    __builtin_amdgcn_s_setprio(3);
     const int64_t s0 = ui.s0, p0 = ui.p0;
     const int nst = ui.nst, npairs = ui.npairs, ngr = ui.ngr, ngc = ui.ngc;
     const int nr0 = ui.nr0, nr1 = ui.nr1, nr2 = ui.nr2, nr3 = ui.nr3;
@@ -1064,19 +1102,20 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
     // uses it, so a load has kLag stages to arrive; every load is unconditional (clamped
     // indices, results masked), which keeps the loop straight-line.  Lane (p, slot):
     // middle cluster p of the stage, slot 0..3 row members, 4..7 column members.
-    constexpr int kLag = 4;
+    constexpr int kLag = 4, kCopies = 64 / CW;
     const int32_t *const stf = g.stage_first + s0;
     const int32_t *const ptab = (lane & 7) < 4 ? g.pair_a + p0 : g.pair_b + p0;
     const int tp = lane >> 3, tslot = lane & 7, tk = tslot & 3;
     const bool tvalid = tslot < 4 ? tk < ngr : tk < ngc;
     int nslot[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) nslot[q] = lane < 32 ? sel4(q, nr0, nr1, nr2, nr3) : sel4(q, nc0, nc1, nc2, nc3);
+    for (int q = 0; q < 4; ++q)
+        nslot[q] = (lane < 32 ? sel4(q, nr0, nr1, nr2, nr3) : sel4(q, nc0, nc1, nc2, nc3)) * (OZ ? 1 : ES);
     // The loads of the loop go straight to LDS (one staging set per phase), so the
     // wave waits for them explicitly: each phase issues exactly four load instructions
-    // (offsets 16 B and cluster size of the entries, entries, bounds), after the four
+    // (offsets 16 B and cluster size of the entries, entries, bounds), after the kCopies
     // shared-fragment copies with SHARE, and at the start of a phase vmcnt <= 4 (kLag - 1)
-    // (8 (kLag - 1) with SHARE) means the set loaded kLag phases ago has landed.  A copy
+    // ((kCopies + 4) (kLag - 1) with SHARE) means the set loaded kLag phases ago has landed.  A copy
     // for stage t is issued in phase t - LEAD, so it has landed at the start of phase
     // t - LEAD + kLag and is visible to the consumers from barrier t - LEAD + kLag + 1 on,
     // no later than barrier t when LEAD >= kLag + 1.
@@ -1128,6 +1167,37 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
             T->level = kb > 0 ? lev0 : -1;
         }
     };
+    // ATab writer shared by both paths: lane kk writes k row kk of the four row members
+    // (lanes below 32) or column members; off_of(sl) is the tile offset of slot sl
+    const uint64_t opnd = reinterpret_cast<uint64_t>(lane < 32 ? A : B);
+    const uint64_t zpage = reinterpret_cast<uint64_t>(g_zero_page);
+    const int nq = max(ngr, ngc);                  // slots past it never have a tile
+    if constexpr (!OZ) {
+        for (int t = 0; t < LEAD + 1; ++t)
+            for (int q = nq; q < 4; ++q) ring[t].adr[(lane < 32 ? 0 : 4) + q][lane & 31] = zpage;
+    }
+    auto write_adr = [&](Rec *T, int kk, bool rows, bool live, int kkm, int ks, auto &&off_of) {
+        if constexpr (!OZ) {
+            int act = 0;
+            uint64_t *const dst = &T->adr[rows ? 0 : 4][kk];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q >= nq) break;
+                const int64_t o = off_of((rows ? 0 : 4) + q);
+                const uint64_t a = opnd + (uint64_t)o * ES + (uint32_t)__mul24(kkm, nslot[q]);
+                const bool on = live && (int32_t)(o >> 32) >= 0;
+                dst[q * (kKS + 4)] = on ? a : zpage;
+                if constexpr (SHARE) {
+                    const uint64_t b = __builtin_amdgcn_ballot_w64(on);
+                    act |= ((uint32_t)b != 0 ? 1 << q : 0) | ((b >> 32) != 0 ? 16 << q : 0);
+                }
+            }
+            if (lane == 0) {
+                T->ks = ks;
+                T->act = act;
+            }
+        }
+    };
     auto write_tab = [&](Rec *T, int64_t o_raw, int32_t m_raw, bool ok, int t_np) {
         if constexpr (OZ) {
             const int64_t t_off = (ok && tvalid) ? o_raw : -1;
@@ -1171,12 +1241,7 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
             if (q == mm) { nmm = nmv[q]; kbm = kbv[q]; }
         const int kkm = kk - kbm;
         const bool live = m >= 0 && kkm < nmm;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t o = __shfl(t_off, mm * 8 + (rows ? 0 : 4) + q);
-            T->kofs[kk][(rows ? 0 : 4) + q] = (live && o >= 0) ? o + (int64_t)kkm * nslot[q] : -1;
-        }
-        if (lane == 0) T->ks = kacc;
+        write_adr(T, kk, rows, live, kkm, kacc, [&](int sl) { return __shfl(t_off, mm * 8 + sl); });
         }
     };
     // The same record built from the staging set of the loop: the stage's cluster sizes go
@@ -1210,30 +1275,29 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
         const int m = __builtin_popcount(prefix) - 1;
         const int kkm = kk - (prefix ? 31 - __builtin_clz(prefix) : 0);
         const int mm = m < 0 ? 0 : m;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int sl = (rows ? 0 : 4) + q;
-            const int64_t o = P->off[2 * (mm * 8 + sl)];
-            T->kofs[kk][sl] = (live && o >= 0) ? o + (int64_t)kkm * nslot[q] : -1;
-        }
-        if (lane == 0) T->ks = kb;
+        write_adr(T, kk, rows, live, kkm, kb, [&](int sl) { return P->off[2 * (mm * 8 + sl)]; });
         }
     };
     // copy of the shared fragment of the record just written to ring slot t_slot (the
     // record is re-read from LDS: this wave wrote it, and LDS accesses of a wave are ordered)
     auto share = [&](const Rec *T, int t_slot) {
         if constexpr (SHARE && !OZ) {
-            double *d = sh.dst + t_slot * 512;
-            const int lk = lane >> 4;
+            double *d = uniform_lds(sh.dst + t_slot * 512);
+            const uint64_t rb = (uint32_t)sh.row;
+            constexpr int KR = CW / 2;                 // k rows per copy instruction
+            uint64_t src[kCopies];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t o = T->kofs[4 * (2 * q + sh.kodd) + lk][sh.slot];
-                dma16((sh.ok && o >= 0) ? sh.X + o + sh.ipair : g_zero_word, d + q * 128);
+            for (int q = 0; q < kCopies; ++q) src[q] = T->adr[sh.slot][KR * q + lane / (64 / KR)];
+#pragma unroll
+            for (int q = 0; q < kCopies; ++q) {
+                const void *p = reinterpret_cast<const void *>(src[q] + rb);
+                if constexpr (CW == 16) dma16(p, d + q * 16 * KR);
+                else dma4(p, d + q * 16 * KR);
             }
         } else if constexpr (SHARE && OZ) {
             // the split-precision slices: lane L copies what consumer lane L loads, the k pair
-            // 4 (L / 16) + q of its row (sh.ipair = the row inside the member), 16 bytes
-            double *d = sh.dst + t_slot * 512;
+            // 4 (L / 16) + q of its row (sh.row = the row inside the member), 16 bytes
+            double *d = uniform_lds(sh.dst + t_slot * 512);
             const int lk = lane >> 4;
             const uint4 *const X4 = reinterpret_cast<const uint4 *>(sh.X);
 #pragma unroll
@@ -1241,7 +1305,7 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
                 const int pp = 4 * lk + q;
                 const int64_t o = T->kofs[pp][sh.slot];
                 const int nmu = T->nmu[pp];
-                const void *src = (sh.ok && o >= 0) ? (const void *)(X4 + ((o + (int64_t)sh.ipair * nmu) >> 1))
+                const void *src = (sh.ok && o >= 0) ? (const void *)(X4 + ((o + (int64_t)sh.row * nmu) >> 1))
                                                     : (const void *)g_zero_word;
                 dma16(src, d + q * 128);
             }
@@ -1283,17 +1347,17 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
     lds_barrier();
     int slot = LEAD;                               // ring slot of stage s + LEAD
     auto phase = [&](int s, Staging *P, int32_t &nw, int32_t &no, bool &ko, bool &ke) {
-        // this set's loads have landed: vmcnt(12).  With SHARE a phase issues four copies
+        // this set's loads have landed: vmcnt(12).  With SHARE a phase issues kCopies copies
         // before its four loads while the prologue issued the four sets alone, so phase
-        // q < kLag finds 12 + 4q loads issued after its set (vmcnt(12 + 4q)), every later
-        // phase 24 (vmcnt(24), which also covers the copies of phase s - kLag)
+        // q < kLag finds 12 + kCopies q loads issued after its set, every later phase
+        // 12 + 3 kCopies (which also covers the copies of phase s - kLag)
         if constexpr (SHARE) {
-            if (s >= 3) __builtin_amdgcn_s_waitcnt(0x4F78);          // vmcnt(24)
-            else if (s == 2) __builtin_amdgcn_s_waitcnt(0x4F74);     // vmcnt(20)
-            else if (s == 1) __builtin_amdgcn_s_waitcnt(0x4F70);     // vmcnt(16)
-            else __builtin_amdgcn_s_waitcnt(0x0F7C);                 // vmcnt(12)
+            if (s >= 3) __builtin_amdgcn_s_waitcnt(vmcnt_at_most(12 + 3 * kCopies));
+            else if (s == 2) __builtin_amdgcn_s_waitcnt(vmcnt_at_most(12 + 2 * kCopies));
+            else if (s == 1) __builtin_amdgcn_s_waitcnt(vmcnt_at_most(12 + kCopies));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_at_most(12));
         } else {
-            __builtin_amdgcn_s_waitcnt(0x0F7C);
+            __builtin_amdgcn_s_waitcnt(vmcnt_at_most(12));
         }
         const int32_t m = P->nm[lane];
         const int32_t er = P->ent[lane];
@@ -1324,12 +1388,261 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
     __builtin_amdgcn_s_waitcnt(0);                 // let the last loads land before the wave ends
 }
 
-template <int WAVES, bool PAIRED>
-__global__ __launch_bounds__(WAVES * 64) void k_mgemm_thin(GroupArgs g, const double *__restrict__ A,
-                                                          const double *__restrict__ B, double *__restrict__ C)
+// What the register-direct FP64 kernels know of their unit.
+struct ThinUnit {
+    int u, sr, sc, ngr, ngc;
+    int nr[4], nc[4];
+    int64_t s0, p0;
+    int nst, npairs;
+    __device__ ThinUnit(const GroupArgs &g, int64_t uidx)
+    {
+        u = g.unit_order[g.first + uidx];
+        const int gr = g.unit_gr[u], gc = g.unit_gc[u];
+        sr = g.grp_s[gr]; sc = g.grp_s[gc];
+        ngr = g.grp_g[gr]; ngc = g.grp_g[gc];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            nr[q] = q < ngr ? g.nfun[g.grp_mem[gr * 4 + q]] : 0;
+            nc[q] = q < ngc ? g.nfun[g.grp_mem[gc * 4 + q]] : 0;
+        }
+        s0 = g.stage_off[u]; p0 = g.pair_off[u];
+        nst = (int)(g.stage_off[u + 1] - s0);
+        npairs = (int)(g.pair_off[u + 1] - p0);
+    }
+    __device__ int nrow(int q) const { return sel4(q, nr[0], nr[1], nr[2], nr[3]); }
+    __device__ int ncol(int q) const { return sel4(q, nc[0], nc[1], nc[2], nc[3]); }
+    __device__ UnitInfo info() const
+    {
+        return {s0, p0, nst, npairs, ngr, ngc, nr[0], nr[1], nr[2], nr[3], nc[0], nc[1], nc[2], nc[3]};
+    }
+    // result v of member functions (kr, ii) x (kc, jj), stored where it belongs to S
+    __device__ void store(const GroupArgs &g, double *C, int kr, int ii, int kc, int jj, double v) const
+    {
+        if (kr >= ngr || kc >= ngc) return;
+        const int n = nrow(kr & 3);
+        const int t = g.unit_out[u * 16 + kr * 4 + kc];
+        if (t >= 0 && ii < n && jj < ncol(kc & 3)) C[g.tile_off[t] + (int64_t)jj * n + ii] = v;
+    }
+};
+
+// Units of a single 16 x 16 block: one consumer wave, one record wave.  Bound by the vector
+// memory path (16 cycles of the CU per load instruction whatever its lanes' pattern, two
+// loads per 16-cycle share of an MFMA) and, on large patterns, by the reads of the column
+// side that miss L2.
+__global__ __launch_bounds__(128) void k_mgemm_thin(GroupArgs g, const double *__restrict__ A,
+                                                   const double *__restrict__ B, double *__restrict__ C)
 {
     extern __shared__ double lds[];
-    KTab *ring = reinterpret_cast<KTab *>(lds);
+    ATab *ring = reinterpret_cast<ATab *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if ((int64_t)blockIdx.x >= g.count) return;
+    const ThinUnit un(g, blockIdx.x);
+    constexpr int LEAD = 3, kSlots = LEAD + 1;
+    if (wave == 1) {
+        record_producer<LEAD, false, 8>(g, un.info(), lds, ring, lane, SharedSide{}, A, B);
+        return;
+    }
+    // A lane loads its own row (column) of A (B) at every k row; rows past the member's end
+    // repeat its last one, since a result row depends on its own operand row alone and
+    // those are not stored.
+    const int lr = lane & 15, lk = lane >> 4;
+    const int ka = lr / un.sr, kb = lr / un.sc;        // below 4; members past the group's end have no tiles
+    const int64_t ia = max(0, min(lr - ka * un.sr, un.nrow(ka) - 1));
+    const int64_t jb = max(0, min(lr - kb * un.sc, un.ncol(kb) - 1));
+    // A stage's 8 k steps are loaded in quarters of two steps, into a ring of eight
+    // register sets (two stages): a quarter is computed while the seven loaded after it
+    // are in flight, and its set is then refilled with the same quarter two stages on.
+    // The lanes load 8 bytes each: 16-byte loads of row pairs need a swap between lanes
+    // for every value, four vector instructions per MFMA more.
+    typedef double dbl2 __attribute__((ext_vector_type(2)));
+    dbl2 qa[8], qb[8];
+    auto load_q = [&](const ATab *T, int q, dbl2 &va, dbl2 &vb) {
+        va.x = load_at<double>(T->adr[ka][8 * q + lk], ia);
+        va.y = load_at<double>(T->adr[ka][8 * q + 4 + lk], ia);
+        vb.x = load_at<double>(T->adr[4 + kb][8 * q + lk], jb);
+        vb.y = load_at<double>(T->adr[4 + kb][8 * q + 4 + lk], jb);
+    };
+    // two accumulators (even and odd k steps), so that consecutive MFMAs of a wave do not
+    // wait for each other; they are added once at the end
+    dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0}, acc1 = dbl4{0.0, 0.0, 0.0, 0.0};
+    // rows at and past the stage's k count load zeros, so every k step runs
+    // unconditionally: straight-line code lets each MFMA wait for its own loads only
+    auto comp_q = [&](const dbl2 &va, const dbl2 &vb) {
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(va.x, vb.x, acc, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(va.y, vb.y, acc1, 0, 0, 0);
+    };
+    // stage s is in sets 4 (s & 1) .. 4 (s & 1) + 3; past the last stage the records have
+    // no rows, so the refills are unconditional and load zeros.  Units have an even
+    // number of stages, so the loop body (two stages) has no exit in its middle, which
+    // would make the compiler wait for loads at the loop head that are still in flight.
+    // Loads are issued in ring order (the loop's waits count on set 0 being the oldest).
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        load_q(&ring[q >> 2], q & 3, qa[q], qb[q]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int slot = 2;                                      // ring slot of stage s + 2
+    for (int s = 0; s < un.nst; s += 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int q = 4 * h; q < 4 * h + 4; ++q) {
+                comp_q(qa[q], qb[q]);
+                load_q(&ring[slot], q & 3, qa[q], qb[q]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            slot = slot == kSlots - 1 ? 0 : slot + 1;
+            lds_barrier();
+        }
+    }
+    acc += acc1;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {                      // register r: row 4r + lk, column lr
+        const int kr = (4 * r + lk) / un.sr;
+        un.store(g, C, kr, 4 * r + lk - kr * un.sr, kb, lr - kb * un.sc, acc[r]);
+    }
+}
+
+// Units with a single 16-row side and 2 to 8 blocks on the other (small clusters x leaf
+// group, either way round).  One consumer wave per 32 rows of the wide side plus a record
+// wave, which also copies the 16-row side of a stage into LDS.  The lane loads two adjacent
+// rows of the wide side at once: they belong to two output blocks, one of the even and one
+// of the odd rows, so 16 bytes per lane need no swap between lanes, and one load serves two
+// MFMAs (a load instruction takes 16 cycles of the CU's vector memory path, as long as an
+// MFMA of one of its four SIMDs; with one load per MFMA that path was 75 % busy and the
+// matrix pipe 44 %).  ALIGNED: a wave's rows are one member (clusters of 24 functions and
+// more), so that it skips exactly the stages without one of that member's tiles; smaller
+// clusters are covered 32 group rows at a time.  W16: every cluster size even (else the
+// rows are loaded 8 bytes at a time).  The 16-row side is the first operand of the MFMA
+// whichever it is: with shared columns the block is computed transposed.
+constexpr int kSideLead = 5;
+constexpr size_t side_lds_bytes() { return ring_bytes<kSideLead>() + (kSideLead + 1) * 4096; }
+
+template <bool W16>
+__global__ __launch_bounds__(320, 6) void k_mgemm_side(GroupArgs g, const double *__restrict__ A,
+                                                      const double *__restrict__ B, double *__restrict__ C)
+{
+    extern __shared__ double lds[];
+    ATab *ring = reinterpret_cast<ATab *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if ((int64_t)blockIdx.x >= g.count) return;
+    const ThinUnit un(g, blockIdx.x);
+    constexpr int LEAD = kSideLead, kSlots = LEAD + 1;
+    double *const shr = lds + ring_bytes<LEAD>() / sizeof(double);
+    const bool shA = g.RB == 1;                        // the shared side: rows (else columns)
+    const int lr = lane & 15, lk = lane >> 4;
+    if (wave == (int)(blockDim.x >> 6) - 1) {
+        // the lane's part of a copied k row: a row pair (W16) or half a row; pairs past the
+        // member's end repeat its last one, members past the group's end have no tiles
+        const int ssz = shA ? un.sr : un.sc, x = W16 ? 2 * (lane & 7) : (lane & 31) >> 1, kx = x / ssz;
+        const int n = shA ? un.nrow(kx & 3) : un.ncol(kx & 3);
+        SharedSide sh{};
+        sh.dst = shr;
+        sh.slot = (shA ? 0 : 4) + (kx & 3);
+        sh.row = 8 * max(0, min(x - kx * ssz, n - (W16 ? 2 : 1))) + (W16 ? 0 : 4 * (lane & 1));
+        record_producer<LEAD, true, 8, ATab, W16 ? 16 : 4>(g, un.info(), lds, ring, lane, sh, A, B);
+        return;
+    }
+    const int osz = shA ? un.sc : un.sr;               // the wave's own (wide) side
+    const bool aligned = osz >= 24;
+    const int x = aligned ? 2 * lr : 32 * wave + 2 * lr;   // the lane's rows: x and x + 1
+    const int ko = aligned ? wave : min(x / osz, 3);
+    const int xi = aligned ? x : x - ko * osz;         // row inside the member
+    const int no = shA ? un.ncol(ko & 3) : un.nrow(ko & 3);
+    const int oslot = (shA ? 4 : 0) + ko;
+    const uint64_t o0 = 8 * max(0, min(xi, no - (W16 ? 2 : 1))), o1 = 8 * max(0, min(xi + 1, no - 1));
+    const int m0 = aligned ? wave : 32 * wave / osz, m1 = aligned ? wave : min((32 * wave + 31) / osz, 3);
+    const int omask = (((2 << m1) - 1) & ~((1 << m0) - 1)) << (shA ? 4 : 0);
+    typedef double dbl2 __attribute__((ext_vector_type(2)));
+    // One stage of operands in registers: a k step is computed, then refilled with the same
+    // step of the next stage.  (Two stages took 128 registers, which let only two
+    // workgroups share a CU, their first and last waves on one SIMD.)  Past the last stage
+    // the records have no rows, so the refills are unconditional and load zeros.
+    dbl2 qo[8];
+    dbl4 ax = dbl4{0.0, 0.0, 0.0, 0.0}, ay = dbl4{0.0, 0.0, 0.0, 0.0};
+    auto load_own = [&](uint64_t ad, dbl2 &v) {
+        if constexpr (W16) {
+            v = load_at<dbl2>(ad + o0, 0);
+        } else {
+            v.x = load_at<double>(ad + o0, 0);
+            v.y = load_at<double>(ad + o1, 0);
+        }
+    };
+    lds_barrier();
+    int act = __builtin_amdgcn_readfirstlane(ring[0].act & omask);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        load_own(ring[0].adr[oslot][4 * t + lk], qo[t]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int slot = 1, shs = 0;                             // ring slots of stages s + 1 and s
+    for (int s = 0; s < un.nst; ++s) {
+        const double *sp = shr + shs * 512 + lane;
+        const uint64_t *ap = &ring[slot].adr[oslot][lk];
+        const int next = ring[slot].act & omask;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            double sv[4];
+            uint64_t ad[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) sv[t] = sp[(4 * h + t) * 64];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ad[t] = ap[4 * (4 * h + t)];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                dbl2 &o = qo[4 * h + t];
+                if (act != 0) {
+                    ax = __builtin_amdgcn_mfma_f64_16x16x4f64(sv[t], o.x, ax, 0, 0, 0);
+                    ay = __builtin_amdgcn_mfma_f64_16x16x4f64(sv[t], o.y, ay, 0, 0, 0);
+                }
+                load_own(ad[t], o);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        act = __builtin_amdgcn_readfirstlane(next);
+        slot = slot == kSlots - 1 ? 0 : slot + 1;
+        shs = shs == kSlots - 1 ? 0 : shs + 1;
+        lds_barrier();
+    }
+    // register r: function 4r + lk of the shared side, row x (ax) and x + 1 (ay) of the own side
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int ssz = shA ? un.sr : un.sc, ks = (4 * r + lk) / ssz, is = 4 * r + lk - ks * ssz;
+        if (shA) {
+            un.store(g, C, ks, is, ko, xi, ax[r]);
+            un.store(g, C, ks, is, ko, xi + 1, ay[r]);
+        } else {
+            un.store(g, C, ko, xi, ks, is, ax[r]);
+            un.store(g, C, ko, xi + 1, ks, is, ay[r]);
+        }
+    }
+}
+
+// ------------------------------------------------------------------ wide units (5 to 7 blocks a side)
+// Units of 5 to 7 blocks on both sides with every cluster size even (leaf groups).  Bound
+// by the FP64 matrix pipe and the waits between its bursts: the panels of a stage come
+// through LDS, so the vector memory is far from busy.  Seven consumer waves own a block
+// row each (1 x CB patches); the eighth keeps the stage records and owns no block.  A
+// stage is run in halves of 16 k rows, so that the double-buffered panels take 64 KB and
+// a patch's fragments few registers, and two workgroups share a CU: one's MFMAs run while
+// the other waits at its barrier for panels.  Every wave gathers two rows of each panel
+// per half, straight to LDS (lane L the rows 2L, 2L + 1 of the group), from the address
+// the record holds for its member and k row.
+constexpr int kHS = 16;      // k rows per panel buffer
+constexpr int kWX = 128;     // panel row stride
+constexpr int kWB = 7;       // largest number of blocks a side
+constexpr size_t wide_lds_bytes() { return 2 * sizeof(double) * kHS * 2 * kWX + 2 * sizeof(ATab); }
+
+__global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double *__restrict__ A,
+                                                       const double *__restrict__ B, double *__restrict__ C)
+{
+    extern __shared__ double lds[];
+    constexpr int PD = kHS * 2 * kWX;                  // doubles of one buffer (A rows, then B columns)
+    ATab *const tab = reinterpret_cast<ATab *>(lds + 2 * PD);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t uidx = blockIdx.x;
@@ -1338,208 +1651,216 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_thin(GroupArgs g, const do
     const int gr = g.unit_gr[u], gc = g.unit_gc[u];
     const int sr = g.grp_s[gr], sc = g.grp_s[gc];
     const int ngr = g.grp_g[gr], ngc = g.grp_g[gc];
-    const int nr0 = g.nfun[g.grp_mem[gr * 4]];
-    const int nr1 = ngr > 1 ? g.nfun[g.grp_mem[gr * 4 + 1]] : 0;
-    const int nr2 = ngr > 2 ? g.nfun[g.grp_mem[gr * 4 + 2]] : 0;
-    const int nr3 = ngr > 3 ? g.nfun[g.grp_mem[gr * 4 + 3]] : 0;
-    const int nc0 = g.nfun[g.grp_mem[gc * 4]];
-    const int nc1 = ngc > 1 ? g.nfun[g.grp_mem[gc * 4 + 1]] : 0;
-    const int nc2 = ngc > 2 ? g.nfun[g.grp_mem[gc * 4 + 2]] : 0;
-    const int nc3 = ngc > 3 ? g.nfun[g.grp_mem[gc * 4 + 3]] : 0;
-    const int nblk = g.RB * g.CB;
-    const int producer = WAVES - 1;
+    auto fun = [&](int gg, int ng, int q) { return q < ng ? g.nfun[g.grp_mem[gg * 4 + q]] : 0; };
+    const int nr0 = fun(gr, ngr, 0), nr1 = fun(gr, ngr, 1), nr2 = fun(gr, ngr, 2), nr3 = fun(gr, ngr, 3);
+    const int nc0 = fun(gc, ngc, 0), nc1 = fun(gc, ngc, 1), nc2 = fun(gc, ngc, 2), nc3 = fun(gc, ngc, 3);
     const int64_t s0 = g.stage_off[u], p0 = g.pair_off[u];
-    const int nst = (int)(g.stage_off[u + 1] - s0), npairs = (int)(g.pair_off[u + 1] - p0);
-    const int lr = lane & 15, lk = lane >> 4;
-
-    // SHARE (several consumer waves, every cluster size even): the record wave copies the
-    // shared 16-row side into LDS five stages ahead and the consumers load only their own
-    // block from global memory
-    constexpr bool SHARE = WAVES > 2 && PAIRED;
-    constexpr int LEAD = SHARE ? 5 : 3;
-    constexpr int kSlots = LEAD + 1;
-    double *const shr = lds + ring_bytes<LEAD>() / sizeof(double);
-    const bool shA = g.RB == 1;                        // the shared side: rows (else columns)
-    const bool odd = (lr & 1) != 0;
-    if (wave == producer) {
-        const UnitInfo ui{s0, p0, nst, npairs, ngr, ngc, nr0, nr1, nr2, nr3, nc0, nc1, nc2, nc3};
-        SharedSide sh{};
-        if constexpr (SHARE) {
-            const int ssz = shA ? sr : sc, sng = shA ? ngr : ngc;
-            const int kx = lr / ssz, ix = lr - kx * ssz;
-            sh.X = shA ? A : B;
-            sh.dst = shr;
-            sh.slot = (shA ? 0 : 4) + (kx & 3);
-            sh.ipair = odd ? ix - 1 : ix;
-            sh.kodd = odd ? 1 : 0;
-            sh.ok = kx < sng && ix < (shA ? sel4(kx & 3, nr0, nr1, nr2, nr3) : sel4(kx & 3, nc0, nc1, nc2, nc3));
-        }
-        record_producer<LEAD, SHARE>(g, ui, lds, ring, lane, sh);
-        return;
-    }
-    if (wave >= nblk) {                                // no block: take part in the barriers only
-        lds_barrier();
-        for (int s = 0; s < nst; ++s) lds_barrier();
-        return;
-    }
-    // ---- consumer: block (rb, cb)
-    const int rb = g.RB == 1 ? 0 : wave, cb = g.RB == 1 ? wave : 0;
-    const int ra = 16 * rb + lr, kra = ra / sr, ia = ra - kra * sr;
-    const bool oka = kra < ngr && ia < sel4(kra & 3, nr0, nr1, nr2, nr3);
-    const int slota = kra & 3;
-    const int cbb = 16 * cb + lr, kcb = cbb / sc, jb = cbb - kcb * sc;
-    const bool okb = kcb < ngc && jb < sel4(kcb & 3, nc0, nc1, nc2, nc3);
-    const int slotb = 4 + (kcb & 3);
-    const double *const zero = g_zero_word;
-    // A stage's 8 k steps are loaded in quarters of two steps, into a ring of eight
-    // register sets (two stages): a quarter is computed while the seven loaded after it
-    // are in flight, and its set is then refilled with the same quarter two stages on.
-    // PAIRED (every cluster size even): lanes 2m and 2m + 1 load the two rows (2m, 2m + 1)
-    // of one k column with one 16-byte load each, the even lane at k step j, the odd lane
-    // at k step j + 1; one value is swapped between them when the quarter is computed.
-    // Without PAIRED a lane loads its own row at both steps.
-    typedef double dbl2 __attribute__((ext_vector_type(2)));
-    const int iap = PAIRED && odd ? ia - 1 : ia, jbp = PAIRED && odd ? jb - 1 : jb;
-    auto load_q = [&](const KTab *T, int q, dbl2 &va, dbl2 &vb) {
-        if constexpr (PAIRED) {
-            const int k = 4 * (2 * q + (odd ? 1 : 0)) + lk;
-            const int64_t oa = T->kofs[k][slota], ob = T->kofs[k][slotb];
-            va = *reinterpret_cast<const dbl2 *>((oka && oa >= 0) ? A + oa + iap : zero);
-            vb = *reinterpret_cast<const dbl2 *>((okb && ob >= 0) ? B + ob + jbp : zero);
-        } else {
+    const int nst = (int)(g.stage_off[u + 1] - s0);
+    // this lane's row pair of either panel: its member (past the group's end: a slot without
+    // tiles, so zeros) and byte offset in the member's column (past the member's end its
+    // last pair again; those results are not stored)
+    const int ka = min(2 * lane / sr, 3), kb = min(2 * lane / sc, 3);
+    const uint32_t ba = 8 * max(0, min(2 * lane - ka * sr, sel4(ka, nr0, nr1, nr2, nr3) - 2));
+    const uint32_t bb = 8 * max(0, min(2 * lane - kb * sc, sel4(kb, nc0, nc1, nc2, nc3) - 2));
+    auto dma16 = [&](uint64_t src, double *dst) {
+        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(src),
+                                         (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+    };
+    auto half_rows = [](int ks, int h) { return max(0, min(ks - kHS * h, kHS)); };
+    // rows wave and wave + 8 of the panels of half h (whole k steps; rows past the stage's
+    // last cluster are zeros)
+    auto gather = [&](const ATab *T, int h, int rows, double *buf) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int k = 4 * (2 * q + h) + lk;
-                const int64_t oa = T->kofs[k][slota], ob = T->kofs[k][slotb];
-                va[h] = *((oka && oa >= 0) ? A + oa + ia : zero);
-                vb[h] = *((okb && ob >= 0) ? B + ob + jb : zero);
+        for (int r = 0; r < 2; ++r) {
+            const int k = wave + 8 * r;
+            if (k < ((rows + 3) & ~3)) {
+                dma16(T->adr[ka][kHS * h + k] + ba, buf + k * kWX);
+                dma16(T->adr[4 + kb][kHS * h + k] + bb, buf + (kHS + k) * kWX);
             }
         }
     };
-    // SHARE: the wave's own side only (the block of the wide side it computes)
-    const double *const own = shA ? B : A;
-    const bool ook = shA ? okb : oka;
-    const int oslot = shA ? slotb : slota, oip = shA ? jbp : iap;
-    auto load_own = [&](const KTab *T, int q, dbl2 &v) {
-        const int64_t o = T->kofs[4 * (2 * q + (odd ? 1 : 0)) + lk][oslot];
-        const bool live = ook && o >= 0;
-        v = *reinterpret_cast<const dbl2 *>(live ? own + o + oip : zero);
-        return live;
+    auto sync = [&]() {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
     };
-    // two accumulators (even and odd k steps), so that consecutive MFMAs of a wave do not
-    // wait for each other; they are added once at the end
-    dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0}, acc1 = dbl4{0.0, 0.0, 0.0, 0.0};
-    // rows at and past the stage's k count have no record (offset -1) and load zeros, so
-    // every k step runs unconditionally: straight-line code lets each MFMA wait for its
-    // own loads only
-    // even lane: (x, partner's x), odd lane: (partner's y, y); each moved value has one
-    // use, so the compiler folds the lane move into the select
-    auto unpair = [&](const dbl2 &v, double &f0, double &f1) {
-        const double px = swap_adjacent(v.x), py = swap_adjacent(v.y);
-        f0 = odd ? py : v.x;
-        f1 = odd ? v.y : px;
-    };
-    auto comp_q = [&](const dbl2 &va, const dbl2 &vb) {
-        double a0 = va.x, a1 = va.y, b0 = vb.x, b1 = vb.y;
-        if constexpr (PAIRED) {
-            unpair(va, a0, a1);
-            unpair(vb, b0, b1);
-        }
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc1, 0, 0, 0);
-    };
-    // stage s is in sets 4 (s & 1) .. 4 (s & 1) + 3; past the last stage the records have
-    // no rows, so the refills are unconditional and load zeros.  Units have an even
-    // number of stages, so the loop body (two stages) has no exit in its middle, which
-    // would make the compiler wait for loads at the loop head that are still in flight.
-    // Loads are issued in ring order (the loop's waits count on set 0 being the oldest).
-    if constexpr (SHARE) {
-        // A stage in which no function of the wave's own block meets a middle cluster of
-        // the stage adds only zeros: its MFMAs are skipped (a wave-uniform branch; the
-        // flag is taken from the lanes' record entries when the stage's loads are issued).
-        dbl2 qo[8];
-        bool act[2];
-        lds_barrier();
+    if (wave == 7) {
+        // ---- record wave: the records are fetched in three steps (bounds, union entries,
+        // offsets), one step per stage, each consuming loads of earlier stages only
+        __builtin_amdgcn_s_setprio(3);                 // ahead of the MFMAs of its SIMD's other waves
+        const int npairs = (int)(g.pair_off[u + 1] - p0);
+        const int32_t *const stf = g.stage_first + s0;
+        const int32_t *const ptab = (lane & 7) < 4 ? g.pair_a + p0 : g.pair_b + p0;
+        const int tp = lane >> 3, tslot = lane & 7, tk = tslot & 3;
+        const bool tvalid = tslot < 4 ? tk < ngr : tk < ngc;
+        const int kk = lane & 31;
+        const bool rows = lane < 32;
+        const uint64_t opnd = reinterpret_cast<uint64_t>(rows ? A : B);
+        const uint64_t zpage = reinterpret_cast<uint64_t>(g_zero_page);
+        int nslot[4];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            bool live = false;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                live |= load_own(&ring[h], q, qo[4 * h + q]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            act[h] = __builtin_amdgcn_ballot_w64(live) != 0;
-        }
-        int slot = 2, shs = 0;                         // ring slots of stages s + 2 and s
-        auto half = [&](int h) {
-            const int base = 4 * h;
-            const dbl2 *sp = reinterpret_cast<const dbl2 *>(shr + shs * 512) + lane;
-            dbl2 sv[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sv[q] = sp[q * 64];
-            const bool run = act[h];
-            bool live = false;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (run) {
-                    const dbl2 va = shA ? sv[q] : qo[base + q], vb = shA ? qo[base + q] : sv[q];
-                    comp_q(va, vb);
-                }
-                live |= load_own(&ring[slot], q, qo[base + q]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            act[h] = __builtin_amdgcn_ballot_w64(live) != 0;
-            slot = slot == kSlots - 1 ? 0 : slot + 1;
-            shs = shs == kSlots - 1 ? 0 : shs + 1;
-            lds_barrier();
+        for (int q = 0; q < 4; ++q) nslot[q] = rows ? sel4(q, nr0, nr1, nr2, nr3) : sel4(q, nc0, nc1, nc2, nc3);
+        auto load_bounds = [&](int st, int32_t &fbe) {
+            fbe = 0;
+            if (st >= nst || lane > 1) return;
+            fbe = lane == 0 || st + 1 < nst ? stf[st + lane] : npairs;
         };
-        for (int s = 0; s < nst; s += 2) {
-            half(0);
-            half(1);
-        }
-    } else {
-        dbl2 qa[8], qb[8];
-        lds_barrier();
+        auto load_entry = [&](int32_t fb, int np, int32_t &e) {
+            e = -1;
+            if (tp < np) e = ptab[fb + tp];
+        };
+        auto load_offsets = [&](int32_t e, int64_t &off, int32_t &nm) {
+            off = -1;
+            nm = 0;
+            if (e < 0) return;
+            if (tvalid) off = g.gl_offd[(int64_t)e * 4 + tk];
+            if (tslot == 0) nm = g.gl_nm[e];
+        };
+        auto fb_of = [&](int32_t v) { return __builtin_amdgcn_readlane(v, 0); };
+        auto np_of = [&](int32_t v) { return __builtin_amdgcn_readlane(v, 1) - __builtin_amdgcn_readlane(v, 0); };
+        auto write_tab = [&](ATab *T, int64_t t_off, int t_nm, int t_np) {
+            uint64_t Bm = 0, Lm = 0;                   // cluster starts, live rows
+            int ks = 0;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            load_q(&ring[q >> 2], q & 3, qa[q], qb[q]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        int slot = 2;                                  // ring slot of stage s + 2
-        for (int s = 0; s < nst; s += 2) {
+            for (int q = 0; q < kSP; ++q) {
+                const int nmq = __builtin_amdgcn_readlane(t_nm, q * 8);
+                if (q < t_np) {
+                    Bm |= 1ull << ks;
+                    Lm |= ((1ull << nmq) - 1) << ks;
+                    ks += nmq;
+                }
+            }
+            const bool live = (((uint32_t)Lm >> kk) & 1u) != 0;
+            const uint32_t prefix = (uint32_t)Bm & ((2u << kk) - 1u);
+            const int mm = max(0, __builtin_popcount(prefix) - 1);
+            const int kkm = kk - (prefix ? 31 - __builtin_clz(prefix) : 0);
+            int act0 = 0, act1 = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                comp_q(qa[q], qb[q]);
-                load_q(&ring[slot], q, qa[q], qb[q]);
-                __builtin_amdgcn_sched_barrier(0);     // a quarter's swaps must not move ahead
+                const int sl = (rows ? 0 : 4) + q;
+                const int64_t o = __shfl(t_off, mm * 8 + sl);
+                const bool on = live && o >= 0;
+                T->adr[sl][kk] = on ? opnd + (uint64_t)o * 8 + (uint32_t)(kkm * nslot[q] * 8) : zpage;
+                const uint64_t b = __builtin_amdgcn_ballot_w64(on);
+                act0 |= ((b & 0xFFFFull) != 0 ? 1 << q : 0) | ((b >> 32 & 0xFFFFull) != 0 ? 16 << q : 0);
+                act1 |= ((b >> 16 & 0xFFFFull) != 0 ? 1 << q : 0) | ((b >> 48) != 0 ? 16 << q : 0);
             }
-            slot = slot == kSlots - 1 ? 0 : slot + 1;
-            lds_barrier();
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                comp_q(qa[4 + q], qb[4 + q]);
-                load_q(&ring[slot], q, qa[4 + q], qb[4 + q]);
-                __builtin_amdgcn_sched_barrier(0);
+            if (lane == 0) {
+                T->ks = ks;
+                T->act_half[0] = act0;
+                T->act_half[1] = act1;
             }
-            slot = slot == kSlots - 1 ? 0 : slot + 1;
-            lds_barrier();
+        };
+        int32_t fbe, e, nm;
+        int64_t off;
+        for (int st = 0; st < 2; ++st) {
+            load_bounds(st, fbe);
+            load_entry(fb_of(fbe), np_of(fbe), e);
+            load_offsets(e, off, nm);
+            write_tab(&tab[st], off, nm, np_of(fbe));
         }
+        load_bounds(2, fbe);
+        int np2 = np_of(fbe);
+        load_entry(fb_of(fbe), np2, e);
+        load_offsets(e, off, nm);                      // stage 2
+        load_bounds(3, fbe);
+        int np3 = np_of(fbe);
+        load_entry(fb_of(fbe), np3, e);                // stage 3
+        load_bounds(4, fbe);                           // stage 4
+        sync();
+        int ks = tab[0].ks;
+        gather(&tab[0], 0, half_rows(ks, 0), lds);
+        for (int s = 0; s < nst; ++s) {
+            ATab *T = &tab[s & 1];
+            const ATab *T1 = &tab[(s + 1) & 1];
+            sync();                                    // first half landed
+            gather(T, 1, half_rows(ks, 1), lds + PD);
+            sync();                                    // second half landed, its gathers issued
+            const int np4 = np_of(fbe);
+            const int32_t fb4 = fb_of(fbe);
+            write_tab(T, off, nm, np2);                // stage s + 2
+            load_offsets(e, off, nm);                  // stage s + 3
+            load_entry(fb4, np4, e);                   // stage s + 4
+            load_bounds(s + 5, fbe);                   // stage s + 5
+            np2 = np3;
+            np3 = np4;
+            ks = T1->ks;                               // past the last stage: no rows
+            gather(T1, 0, half_rows(ks, 0), lds);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        return;
     }
-    acc += acc1;
-    // store the block where it belongs to S
-    const int col = 16 * cb + lr;
-    const int kc = col / sc, jj = col - kc * sc;
-    if (kc >= ngc) return;
-    const int ncl = sel4(kc & 3, nc0, nc1, nc2, nc3);
-    if (jj >= ncl) return;
+    const int lr = lane & 15, lk = lane >> 4;
+    const bool active = wave < g.RB;
+    dbl4 acc[kWB];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = 16 * rb + 4 * r + lk;
-        const int kr = row / sr, ii = row - kr * sr;
-        if (kr >= ngr) continue;
-        const int nr = sel4(kr & 3, nr0, nr1, nr2, nr3);
-        const int t = g.unit_out[u * 16 + kr * 4 + kc];
-        if (t >= 0 && ii < nr) C[g.tile_off[t] + (int64_t)jj * nr + ii] = acc[r];
+    for (int j = 0; j < kWB; ++j) acc[j] = dbl4{0.0, 0.0, 0.0, 0.0};
+    // members covering the wave's block row and each block column (bits of act): a block
+    // none of whose row (or column) members has a tile in the half adds only zeros
+    const int m0 = 16 * wave / sr, m1 = min((16 * wave + 15) / sr, 3);
+    const int amask = m0 > 3 ? 0 : ((2 << m1) - 1) & ~((1 << m0) - 1);
+    int bmask[kWB];
+#pragma unroll
+    for (int j = 0; j < kWB; ++j) {
+        const int c0 = 16 * j / sc, c1 = min((16 * j + 15) / sc, 3);
+        bmask[j] = c0 > 3 || j >= g.CB ? 0 : (((2 << c1) - 1) & ~((1 << c0) - 1)) << 4;
+    }
+    const double *const fa0 = lds + lk * kWX + 16 * wave + lr, *const fb0 = lds + (kHS + lk) * kWX + lr;
+    auto compute = [&](int buf, int rows, int act) {
+        const double *pa = fa0 + buf * PD, *pb = fb0 + buf * PD;
+        if (!active || (act & amask) == 0) return;
+        double fa[4], nb[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) fa[t] = pa[4 * t * kWX];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) nb[t] = pb[4 * t * kWX];
+#pragma unroll
+        for (int j = 0; j < kWB; ++j) {
+            double fb[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) fb[t] = nb[t];
+            if (j + 1 < kWB)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) nb[t] = pb[4 * t * kWX + 16 * (j + 1)];
+            if ((act & bmask[j]) != 0) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (4 * t < rows) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[t], fb[t], acc[j], 0, 0, 0);
+            }
+        }
+    };
+    sync();
+    int ks = tab[0].ks;
+    gather(&tab[0], 0, half_rows(ks, 0), lds);
+    for (int s = 0; s < nst; ++s) {
+        const ATab *T = &tab[s & 1], *T1 = &tab[(s + 1) & 1];
+        sync();                                        // first half landed; MFMAs of the last half done
+        const int act0 = __builtin_amdgcn_readfirstlane(T->act_half[0]);
+        const int act1 = __builtin_amdgcn_readfirstlane(T->act_half[1]);
+        const int r0 = half_rows(ks, 0), r1 = half_rows(ks, 1);
+        gather(T, 1, r1, lds + PD);
+        compute(0, r0, act0);
+        sync();                                        // second half landed
+        ks = __builtin_amdgcn_readfirstlane(T1->ks);
+        gather(T1, 0, half_rows(ks, 0), lds);
+        if (r1 > 0) compute(1, r1, act1);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    if (!active) return;
+#pragma unroll
+    for (int j = 0; j < kWB; ++j) {
+        if (j >= g.CB) continue;
+        const int col = 16 * j + lr;
+        const int kc = col / sc, jj = col - kc * sc;
+        if (kc >= ngc || jj >= sel4(kc & 3, nc0, nc1, nc2, nc3)) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 16 * wave + 4 * r + lk;
+            const int kr = row / sr, ii = row - kr * sr;
+            if (kr >= ngr) continue;
+            const int nr = sel4(kr & 3, nr0, nr1, nr2, nr3);
+            const int t = g.unit_out[u * 16 + kr * 4 + kc];
+            if (t >= 0 && ii < nr) C[g.tile_off[t] + (int64_t)jj * nr + ii] = acc[j][r];
+        }
     }
 }
 
@@ -1596,8 +1917,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_f32acc(GroupArgs g, const 
                                                             const float *__restrict__ B, float *__restrict__ C)
 {
     typedef float flt4 __attribute__((ext_vector_type(4)));
+    typedef float flt2 __attribute__((ext_vector_type(2)));
     extern __shared__ double lds[];
-    KTab *ring = reinterpret_cast<KTab *>(lds);
+    ATab *ring = reinterpret_cast<ATab *>(lds);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t uidx = blockIdx.x;
@@ -1623,7 +1945,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_f32acc(GroupArgs g, const 
 
     if (wave == producer) {
         const UnitInfo ui{s0, p0, nst, npairs, ngr, ngc, nr0, nr1, nr2, nr3, nc0, nc1, nc2, nc3};
-        record_producer<2, false>(g, ui, lds, ring, lane, SharedSide{});
+        record_producer<2, false, 4>(g, ui, lds, ring, lane, SharedSide{}, A, B);
         return;
     }
     if (wave >= nconsumer) {
@@ -1633,68 +1955,46 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_f32acc(GroupArgs g, const 
     }
     const int ncb = rows_split ? g.CB : 1;           // column blocks of this wave
     const int rb = rows_split ? wave : 0;
-    const int ra = 16 * rb + lr, kra = ra / sr, ia = ra - kra * sr;
-    const bool oka = kra < ngr && ia < sel4(kra & 3, nr0, nr1, nr2, nr3);
+    // the lane's first row (column) of a load of LW rows inside its member; rows past the
+    // member's end repeat its last ones (results not stored)
+    const int q = lr & 3, ql = lr & (LW - 1);
+    const int ra = 16 * rb + lr, kra = ra / sr;
     const int slota = kra & 3;
-    int jb[MC], slotb[MC], cbv[MC];
-    bool okb[MC];
+    const int64_t ia = max(0, min(ra - kra * sr - ql, sel4(slota, nr0, nr1, nr2, nr3) - LW));
+    int64_t jb[MC];
+    int slotb[MC], cbv[MC];
 #pragma unroll
     for (int c = 0; c < MC; ++c) {
         cbv[c] = rows_split ? min(c, g.CB - 1) : wave;
         const int col = 16 * cbv[c] + lr, kcb = col / sc;
-        jb[c] = col - kcb * sc;
-        okb[c] = kcb < ngc && jb[c] < sel4(kcb & 3, nc0, nc1, nc2, nc3);
+        jb[c] = max(0, min(col - kcb * sc - ql, sel4(kcb & 3, nc0, nc1, nc2, nc3) - LW));
         slotb[c] = 4 + (kcb & 3);
     }
-    const float *const zero = reinterpret_cast<const float *>(g_zero_word);
-    const int q = lr & 3;
     // Fragments of half h (k steps 4h .. 4h + 3) of the stage whose record is T, kept as
     // loaded (LW = 4: rows 4m .. 4m + 3 at k step 4h + q; LW = 2: rows 2m, 2m + 1 at k
     // steps 4h + p and 4h + p + 2, p = l % 2) and put in MFMA order (the quad transpose,
     // or one pair exchange per load) only when the half is computed, so no load is
     // waited for when issued.  LW = 2 needs every cluster size even: a row pair then
     // never straddles two clusters or the end of one, and its 8 bytes are aligned.
-    auto load_half = [&](const KTab *T, int h, flt4 &fa, flt4 (&fb)[MC]) {
+    auto load_side = [&](const ATab *T, int h, int slot, int64_t i, flt4 &f) {
         if constexpr (LW == 2) {
-            const int pp = lr & 1;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int k = 4 * (4 * h + 2 * j + pp) + lk;
-                const int64_t oa = T->kofs[k][slota];
-                const float2 va = *reinterpret_cast<const float2 *>((oka && oa >= 0) ? A + oa + (ia - pp) : zero);
-                fa[2 * j] = va.x;
-                fa[2 * j + 1] = va.y;
-#pragma unroll
-                for (int c = 0; c < MC; ++c) {
-                    const int64_t ob = T->kofs[k][slotb[c]];
-                    const float2 vb =
-                        *reinterpret_cast<const float2 *>((okb[c] && ob >= 0) ? B + ob + (jb[c] - pp) : zero);
-                    fb[c][2 * j] = vb.x;
-                    fb[c][2 * j + 1] = vb.y;
-                }
+                const flt2 v = load_at<flt2>(T->adr[slot][4 * (4 * h + 2 * j + ql) + lk] + 4 * i, 0);
+                f[2 * j] = v.x;
+                f[2 * j + 1] = v.y;
             }
         } else if constexpr (LW == 4) {
-            const int k = 4 * (4 * h + q) + lk;
-            const int64_t oa = T->kofs[k][slota];
-            fa = *reinterpret_cast<const flt4 *>((oka && oa >= 0) ? A + oa + (ia - q) : zero);
-#pragma unroll
-            for (int c = 0; c < MC; ++c) {
-                const int64_t ob = T->kofs[k][slotb[c]];
-                fb[c] = *reinterpret_cast<const flt4 *>((okb[c] && ob >= 0) ? B + ob + (jb[c] - q) : zero);
-            }
+            f = load_at<flt4>(T->adr[slot][4 * (4 * h + ql) + lk] + 4 * i, 0);
         } else {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int k = 4 * (4 * h + t) + lk;
-                const int64_t oa = T->kofs[k][slota];
-                fa[t] = *((oka && oa >= 0) ? A + oa + ia : zero);
-#pragma unroll
-                for (int c = 0; c < MC; ++c) {
-                    const int64_t ob = T->kofs[k][slotb[c]];
-                    fb[c][t] = *((okb[c] && ob >= 0) ? B + ob + jb[c] : zero);
-                }
-            }
+            for (int t = 0; t < 4; ++t) f[t] = load_at<float>(T->adr[slot][4 * (4 * h + t) + lk], i);
         }
+    };
+    auto load_half = [&](const ATab *T, int h, flt4 &fa, flt4 (&fb)[MC]) {
+        load_side(T, h, slota, ia, fa);
+#pragma unroll
+        for (int c = 0; c < MC; ++c) load_side(T, h, slotb[c], jb[c], fb[c]);
     };
     dbl4 acc[MC];
     flt4 a32[MC];
@@ -1964,10 +2264,10 @@ __global__ __launch_bounds__(WAVES * 64, SHARE ? 4 : 1) void k_mgemm_oz(GroupArg
             sh.X = reinterpret_cast<const double *>(shA ? SA : SB);
             sh.dst = shr;
             sh.slot = (shA ? 0 : 4) + (kx & 3);
-            sh.ipair = ix;
+            sh.row = ix;
             sh.ok = kx < sng && ix < (shA ? sel4(kx & 3, nr0, nr1, nr2, nr3) : sel4(kx & 3, nc0, nc1, nc2, nc3));
         }
-        record_producer<LEAD, SHARE, OzTab>(g, ui, lds, ring, lane, sh);
+        record_producer<LEAD, SHARE, 4, OzTab>(g, ui, lds, ring, lane, sh, nullptr, nullptr);
         return;
     }
     // consumers fill the exponent tables (visible after the first barrier)
@@ -2585,27 +2885,25 @@ int launch_gemm_abt(spm_pattern p, const double *A, const double *B, double *C, 
         const size_t lds = 2 * pd * sizeof(double) + 2 * sizeof(KTab);
         if (lds > 160 * 1024) return fail(SPM_EUNSUPPORTED, "grouped product: LDS budget exceeded");
         const dim3 grid((unsigned)L.count);
-        if ((L.rb == 1 || L.cb == 1) && L.rb * L.cb <= 7) {
-            // one side a single block: register-direct kernel, one wave per block plus the
-            // record wave
+        if (L.rb == 1 || L.cb == 1) {
+            // one side a single block: register-direct kernels
             g.WR = g.WC = g.nsplit = 1;
-            // record ring and staging, then with the shared-side copies (8 waves, even
-            // sizes) their ring of six 4 KB slots
-            const bool share = wide && L.rb * L.cb > 1;
-            const size_t ring = share ? ring_bytes<5>() + 6 * 4096 : ring_bytes<3>();
+            const int nb = L.rb * L.cb;
             int st;
-            const void *k;
-            if (L.rb * L.cb == 1) k = wide ? (const void *)k_mgemm_thin<2, true> : (const void *)k_mgemm_thin<2, false>;
-            else k = wide ? (const void *)k_mgemm_thin<8, true> : (const void *)k_mgemm_thin<8, false>;
-            st = launch_grp(k, grid, L.rb * L.cb == 1 ? 128 : 512, ring, s, g, A, B, C);
+            if (nb == 1) st = launch_grp((const void *)k_mgemm_thin, grid, 128, ring_bytes<3>(), s, g, A, B, C);
+            else {
+                // consumers: one per member of the wide side (24 functions or more), or one
+                // per 32 rows; a class may hold units of both kinds
+                const int nc = std::max((nb + 1) / 2, std::min(4, 16 * nb / 24));
+                st = launch_grp(wide ? (const void *)k_mgemm_side<true> : (const void *)k_mgemm_side<false>, grid,
+                                64 * (nc + 1), side_lds_bytes(), s, g, A, B, C);
+            }
             if (st) return st;
             continue;
         }
-        if (L.rb * L.cb == 1) {
-            // one 16 x 16 block: one MFMA wave plus a wave that keeps the stage records
+        if (wide && L.rb >= 5 && L.rb <= kWB && L.cb >= 5 && L.cb <= kWB) {
             g.WR = g.WC = g.nsplit = 1;
-            const void *k = wide ? (const void *)k_mgemm_grp<2, 16, 1, 1> : (const void *)k_mgemm_grp<2, 4, 1, 1>;
-            int st = launch_grp(k, grid, 128, lds, s, g, A, B, C);
+            int st = launch_grp((const void *)k_mgemm_wide, grid, 512, wide_lds_bytes(), s, g, A, B, C);
             if (st) return st;
             continue;
         }
