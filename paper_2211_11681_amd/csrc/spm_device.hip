@@ -504,8 +504,8 @@ __global__ __launch_bounds__(64) void k_mgemm_f32(GemmArgs g, const float *__res
     }
 }
 
-// Positions inside a tile but outside S are set to zero after a product (patterns
-// uploaded entry by entry only).
+// Positions inside a tile but outside S are set to zero after a product of the per-tile and
+// split-precision kernels (patterns uploaded entry by entry only).
 __global__ void k_apply_keep(int64_t ns, int prec, const uint8_t *__restrict__ keep, void *c)
 {
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < ns; e += (int64_t)gridDim.x * blockDim.x) {
@@ -555,6 +555,7 @@ struct GroupArgs {
     const int32_t *stage_first;
     const int64_t *tile_off;
     const int32_t *nfun;
+    const uint8_t *keep;     // entry-level patterns: 0 where a stored position is outside S (else null)
     int64_t first, count;
     int32_t RB, CB;
     int32_t lxa, lxb;        // log2 of the panel row strides
@@ -1003,7 +1004,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
                 if (kr >= ngr2) continue;
                 const int nr = g.nfun[g.grp_mem[gr2 * 4 + kr]];
                 const int t = g.unit_out[u * 16 + kr * 4 + kc];
-                if (t >= 0 && ii < nr) C[g.tile_off[t] + (int64_t)jj * nr + ii] = acc[i][j][r];
+                if (t >= 0 && ii < nr) {
+                    const int64_t e = g.tile_off[t] + (int64_t)jj * nr + ii;
+                    C[e] = g.keep && !g.keep[e] ? 0.0 : acc[i][j][r];
+                }
             }
         }
     }
@@ -1421,7 +1425,10 @@ struct ThinUnit {
         if (kr >= ngr || kc >= ngc) return;
         const int n = nrow(kr & 3);
         const int t = g.unit_out[u * 16 + kr * 4 + kc];
-        if (t >= 0 && ii < n && jj < ncol(kc & 3)) C[g.tile_off[t] + (int64_t)jj * n + ii] = v;
+        if (t >= 0 && ii < n && jj < ncol(kc & 3)) {
+            const int64_t e = g.tile_off[t] + (int64_t)jj * n + ii;
+            C[e] = g.keep && !g.keep[e] ? 0.0 : v;
+        }
     }
 };
 
@@ -1859,7 +1866,10 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double
             if (kr >= ngr) continue;
             const int nr = sel4(kr & 3, nr0, nr1, nr2, nr3);
             const int t = g.unit_out[u * 16 + kr * 4 + kc];
-            if (t >= 0 && ii < nr) C[g.tile_off[t] + (int64_t)jj * nr + ii] = acc[j][r];
+            if (t >= 0 && ii < nr) {
+                const int64_t e = g.tile_off[t] + (int64_t)jj * nr + ii;
+                C[e] = g.keep && !g.keep[e] ? 0.0 : acc[j][r];
+            }
         }
     }
 }
@@ -2055,7 +2065,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_f32acc(GroupArgs g, const 
             if (kr >= ngr) continue;
             const int nr = sel4(kr & 3, nr0, nr1, nr2, nr3);
             const int t = g.unit_out[u * 16 + kr * 4 + kc];
-            if (t >= 0 && ii < nr) C[g.tile_off[t] + (int64_t)jj * nr + ii] = (float)acc[c][r];
+            if (t >= 0 && ii < nr) {
+                const int64_t e = g.tile_off[t] + (int64_t)jj * nr + ii;
+                C[e] = g.keep && !g.keep[e] ? 0.f : (float)acc[c][r];
+            }
         }
     }
 }
@@ -2681,14 +2694,18 @@ __device__ inline void buf_store(__amdgpu_buffer_rsrc_t r, int off, typename Buf
 }
 
 // out = the tiles of in, each transposed into the place of its mirror tile.  One
-// wavefront per run of kTrRun consecutive tiles: lane k loads the descriptors of tile
+// wavefront per run of `run` (at most kTrRun) consecutive tiles: lane k loads the descriptors of tile
 // t0 + k (one coalesced load per table) into LDS.  The run's input is contiguous in
 // storage; it is staged through LDS kTrStage entries (whole tiles) at a time, read in
 // order (coalesced, through a buffer resource of the run's extent, so lanes past its end
 // read 0 without a branch), and every mirror tile is then written in order (coalesced),
 // tile by tile, each lane gathering its entry from LDS.  Staged entry q sits at q + q / 32, so the gathers (stride n_rows)
-// spread over the banks.
+// spread over the banks.  Runs are 64 tiles (one descriptor per lane) where that leaves
+// every wavefront slot of the card (16 per CU at this LDS) a run, else shorter: a run is a
+// serial chain, and 32691 tiles in runs of 64 are 511 wavefronts on 256 CUs (26.7 us; 9.5 in
+// runs of 7).
 constexpr int kTrRun = 64;
+constexpr int64_t kTrWaves = 256 * 16;
 constexpr int kTrStage = 1024;
 constexpr int kTrUnroll = 16;
 static_assert(kTrStage >= kMax * kMax, "a staged group holds at least one whole tile");
@@ -2706,7 +2723,7 @@ __global__ __launch_bounds__(256) void k_transpose(int64_t n_tiles, const int64_
                                                   const int32_t *__restrict__ tile_row,
                                                   const int32_t *__restrict__ tile_col,
                                                   const int32_t *__restrict__ trans, const int32_t *__restrict__ nfun,
-                                                  const T *__restrict__ in, T *__restrict__ out)
+                                                  const T *__restrict__ in, T *__restrict__ out, int run)
 {
     using Word = typename BufWord<T>::type;
     __shared__ int32_t sh_off[4][kTrRun + 1]; // tile starts relative to the run's first entry
@@ -2719,8 +2736,8 @@ __global__ __launch_bounds__(256) void k_transpose(int64_t n_tiles, const int64_
     int64_t *s_dst = sh_dst[w];
     float *s_rnc = sh_rnc[w];
     Word *stage = sh_stage[w];
-    for (int64_t t0 = ((int64_t)blockIdx.x * 4 + w) * kTrRun; t0 < n_tiles; t0 += (int64_t)gridDim.x * 4 * kTrRun) {
-        const int m = (int)min((int64_t)kTrRun, n_tiles - t0);
+    for (int64_t t0 = ((int64_t)blockIdx.x * 4 + w) * run; t0 < n_tiles; t0 += (int64_t)gridDim.x * 4 * run) {
+        const int m = (int)min((int64_t)run, n_tiles - t0);
         const int64_t base = tile_off[t0];
         if (lane < m) {
             const int64_t t = t0 + lane;
@@ -2873,6 +2890,7 @@ int launch_gemm_abt(spm_pattern p, const double *A, const double *B, double *C, 
     g.pair_b = p->d_pair_b.ptr; g.gl_nm = p->d_gl_nm.ptr; g.gl_offd = p->d_gl_offd.ptr;
     g.stage_off = p->d_stage_off.ptr; g.stage_first = p->d_stage_first.ptr; g.tile_off = p->d_tile_off.ptr;
     g.nfun = p->d_nfun.ptr;
+    g.keep = p->d_keep.ptr;
     const bool wide = p->all_even;   // two doubles per lane never straddle a cluster's functions
     for (const auto &L : p->launches) {
         g.first = L.first;
@@ -2950,8 +2968,10 @@ int launch_gemm_abt(spm_pattern p, const double *A, const double *B, double *C, 
 template <typename T>
 int launch_transpose(spm_pattern p, const T *in, T *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_transpose<T>, dim3(grid1d(p->n_tiles, 4 * kTrRun, 16384)), dim3(256), 0, s, p->n_tiles,
-                       p->d_tile_off.ptr, p->d_tile_row.ptr, p->d_tile_col.ptr, p->d_trans.ptr, p->d_nfun.ptr, in, out);
+    const int run = (int)std::max<int64_t>(4, std::min<int64_t>(kTrRun, p->n_tiles / kTrWaves));
+    hipLaunchKernelGGL(k_transpose<T>, dim3(grid1d(p->n_tiles, 4 * run, 16384)), dim3(256), 0, s, p->n_tiles,
+                       p->d_tile_off.ptr, p->d_tile_row.ptr, p->d_tile_col.ptr, p->d_trans.ptr, p->d_nfun.ptr, in, out,
+                       run);
     SPM_HIP(hipGetLastError());
     return SPM_OK;
 }
@@ -3019,6 +3039,7 @@ int gemm_f32acc_ws(spm_pattern p, const float *A, int ta, const float *B, int tb
     g.pair_b = p->d_pair_b.ptr; g.gl_nm = p->d_gl_nm.ptr; g.gl_offd = p->d_gl_offd.ptr;
     g.stage_off = p->d_stage_off.ptr; g.stage_first = p->d_stage_first.ptr; g.tile_off = p->d_tile_off.ptr;
     g.nfun = p->d_nfun.ptr;
+    g.keep = p->d_keep.ptr;
     g.lxa = g.lxb = 4;
     g.WR = g.WC = g.nsplit = 1;
     const int lw = p->all_mult4 ? 4 : p->all_even ? 2 : 1;   // bytes per lane load / 4
@@ -3078,6 +3099,7 @@ int gemm_oz_ws(spm_pattern p, const float *A, int ta, const float *B, int tb, fl
     g.pair_b = p->d_pair_b_lv.ptr; g.gl_nm = p->d_gl_nml.ptr; g.gl_offd = p->d_gl_offT.ptr;
     g.stage_off = p->d_stage_off_lv.ptr; g.stage_first = p->d_stage_first_lv.ptr; g.tile_off = p->d_tile_off.ptr;
     g.nfun = p->d_nfun.ptr;
+    g.keep = p->d_keep.ptr;
     g.lxa = g.lxb = 4;
     g.WR = g.WC = g.nsplit = 1;
     OzArgs z{EA, EB, p->d_cstart.ptr, p->nlev};
@@ -3122,10 +3144,13 @@ int gemm_ws(spm_pattern p, int prec, const void *A, int ta, const void *B, int t
     if (p->n_tiles == 0) return SPM_OK;
     char *w = static_cast<char *>(ws);
     int st;
+    bool masked = false;                               // the kernels zero what lies outside S themselves
     if (prec == SPM_F64) {
+        masked = true;
         st = gemm_grouped_ws(p, static_cast<const double *>(A), ta, static_cast<const double *>(B), tb,
                              static_cast<double *>(C), w, s);
     } else if (prec == SPM_F32ACC && f32acc_grouped(p)) {
+        masked = true;
         st = gemm_f32acc_ws(p, static_cast<const float *>(A), ta, static_cast<const float *>(B), tb,
                             static_cast<float *>(C), w, s);
     } else if (prec == SPM_F32SPLIT && oz_ok(p)) {
@@ -3152,7 +3177,7 @@ int gemm_ws(spm_pattern p, int prec, const void *A, int ta, const void *B, int t
         st = SPM_OK;
     }
     if (st) return st;
-    if (p->d_keep.ptr)
+    if (p->d_keep.ptr && !masked)
         hipLaunchKernelGGL(k_apply_keep, dim3(grid1d(p->n_stored, 256)), dim3(256), 0, s, p->n_stored, prec,
                            p->d_keep.ptr, C);
     SPM_HIP(hipGetLastError());
