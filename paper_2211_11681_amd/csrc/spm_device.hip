@@ -2491,12 +2491,20 @@ __global__ __launch_bounds__(WAVES * 64, SHARE ? 4 : 1) void k_mgemm_oz(GroupArg
 //  - n_nu > 8: v_mfma_f64_16x16x4f64.  Per 16 columns, lane l loads A at row
 //    16 rb + l%16 and X at column cc0 + 16 cb + l%16, both at piece columns
 //    l/16 + 4s (s = 0..3), so every value of A and X is loaded once.
-//  - n_nu <= 8 (where a 16-row MFMA would be mostly padding): plain FMAs.  Lane l takes
-//    piece column l%16 of each chunk and X columns l/16 + 4m, and keeps n_nu x 4 CB sums,
-//    folded over the 16 column lanes at the end; with at most four columns of X, lane l
-//    takes piece column l of each 64-column step and all columns of X, so each entry of
-//    A is loaded once.
-// Four waves per workgroup, so that three workgroups fit on a CU.
+//  - n_nu <= 8 (where a 16-row MFMA would be mostly padding): v_mfma_f64_4x4x4f64, whose
+//    four blocks take the four quarters of 16 piece columns: lane i + 4b + 16k loads row i
+//    of A at column 4b + k, so one load instruction covers 16 columns of four rows, and
+//    X at the same columns, four columns of X per MFMA; the blocks' sums are added at the
+//    end.  A load instruction takes 16 cycles of a CU's vector memory path whatever it
+//    carries, so the entries of A per load decide.  A load of X touches four of its columns
+//    in every quad of lanes, though, and with more than 12 columns the plain FMA form (a
+//    quarter of the entries of A per load, lanes along X) is ahead: N = 65536 in 3D,
+//    5 / 10 / 16 columns 764 / 969 / 1282 us against 911 / 967 / 1073; N = 50000 on the
+//    sphere, 5 / 10 columns 253 / 356 against 580 / 611.
+// Whole steps load at a uniform base plus a constant lane offset, with no vector
+// instruction (they exclude the MFMAs of their SIMD); only a piece's last step tests its
+// columns.  Rows past n_nu and columns of X past r repeat the last one; those results are
+// not stored.  Four waves per workgroup, so that three or more workgroups fit on a CU.
 constexpr int kSpmmWaves = 4;
 
 // load at a uniform base plus a 32-bit byte offset (one VGPR per address)
@@ -2517,47 +2525,57 @@ __device__ __forceinline__ void spmm_mfma(int64_t q, int64_t p1, int nr, int64_t
     for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) d[rb][cb] = dbl4{0.0, 0.0, 0.0, 0.0};
+    uint32_t ao[NRB], xo[CB];                          // lane offsets (bytes)
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) ao[rb] = 8u * (uint32_t)(lk * nr + min(16 * rb + lr, nr - 1));
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) xo[cb] = 8u * (uint32_t)((min(cc0 + 16 * cb + lr, r - 1) - cc0) * n + lk);
+    const double *const xc = X + (int64_t)cc0 * n;
     for (; q < p1; q += kSpmmWaves) {
         const int w = pc_w[q];
-        const double *aq = A + pc_off[q];
-        const int64_t g = pc_g[q];
-        const double *xr[CB];   // uniform: column cc0 + 16 cb of X at the piece's first basis column
-        bool xon[CB];
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            xon[cb] = cc0 + 16 * cb + lr < r;
-            xr[cb] = X + (int64_t)(cc0 + 16 * cb) * n + g;
-        }
-        const uint32_t xl = 8u * (uint32_t)(lr * n);
+        const double *aq = A + pc_off[q], *xq = xc + pc_g[q];
         // U chunks of 16 columns per step, all of their loads in flight together
         constexpr int U = NRB == 1 ? 4 : 2;
-        for (int j0 = 0; j0 < w; j0 += 16 * U) {
-            double av[U][NRB][4], xv[U][CB][4];
+        double av[U][NRB][4], xv[U][CB][4];
+        auto mfmas = [&](int u) {
+#pragma unroll
+            for (int sl = 0; sl < 4; ++sl)
+#pragma unroll
+                for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+                        d[rb][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][rb][sl], xv[u][cb][sl], d[rb][cb], 0, 0, 0);
+        };
+        int j0 = 0;
+        for (; j0 + 16 * U <= w; j0 += 16 * U) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int sl = 0; sl < 4; ++sl) {
-                    const int jc = j0 + 16 * u + lk + 4 * sl;
-                    const bool jon = jc < w;
+                    const int jc = j0 + 16 * u + 4 * sl;
 #pragma unroll
-                    for (int rb = 0; rb < NRB; ++rb) {
-                        const int row = 16 * rb + lr;
-                        av[u][rb][sl] = (jon && row < nr) ? ld_off(aq, 8u * (uint32_t)(jc * nr + row)) : 0.0;
-                    }
+                    for (int rb = 0; rb < NRB; ++rb) av[u][rb][sl] = ld_off(aq + (int64_t)jc * nr, ao[rb]);
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
-                        xv[u][cb][sl] = (jon && xon[cb]) ? ld_off(xr[cb], xl + 8u * (uint32_t)jc) : 0.0;
+                    for (int cb = 0; cb < CB; ++cb) xv[u][cb][sl] = ld_off(xq + jc, xo[cb]);
                 }
+#pragma unroll
+            for (int u = 0; u < U; ++u) mfmas(u);
+        }
+        if (j0 < w) {                                  // the last step, its columns tested
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int sl = 0; sl < 4; ++sl)
+                for (int sl = 0; sl < 4; ++sl) {
+                    const int jc = j0 + 16 * u + 4 * sl;
+                    const bool on = jc + lk < w;
 #pragma unroll
-                    for (int rb = 0; rb < NRB; ++rb)
+                    for (int rb = 0; rb < NRB; ++rb) av[u][rb][sl] = on ? ld_off(aq + (int64_t)jc * nr, ao[rb]) : 0.0;
 #pragma unroll
-                        for (int cb = 0; cb < CB; ++cb)
-                            d[rb][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][rb][sl], xv[u][cb][sl], d[rb][cb],
-                                                                             0, 0, 0);
+                    for (int cb = 0; cb < CB; ++cb) xv[u][cb][sl] = on ? ld_off(xq + jc, xo[cb]) : 0.0;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (j0 + 16 * u < w) mfmas(u);
         }
     }
     // accumulator register k of lane l: row 16 rb + 4 k + l/16, column 16 cb + l%16
@@ -2569,16 +2587,85 @@ __device__ __forceinline__ void spmm_mfma(int64_t q, int64_t p1, int nr, int64_t
             for (int k = 0; k < 4; ++k) red[16 * rb + 4 * k + lk][16 * cb + lr] = d[rb][cb][k];
 }
 
-// CL groups of 64 / CL column lanes: with CL = 4 each group takes 4 CB columns of X (16 CB
-// per pass, the four groups reading the same entries of A); with CL = 1 (at most four
-// columns of X) every lane reads its own column of A, so each entry is loaded once.
-template <int MAXR, int CB, int CL = 4>
+// NG groups of four rows (NG = 1 or 2), XG groups of four columns of X.
+template <int NG, int XG, int CB>
 __device__ __forceinline__ void spmm_thin(int64_t q, int64_t p1, int nr, int64_t n, int r, int cc0,
                                           const int64_t *__restrict__ pc_off, const int64_t *__restrict__ pc_g,
                                           const int32_t *__restrict__ pc_w, const double *__restrict__ A,
                                           const double *__restrict__ X, double (*red)[16 * CB + 1])
 {
-    constexpr int M = 4 * CB, JL = 64 / CL;
+    const int lane = threadIdx.x & 63, i = lane & 3, b = (lane >> 2) & 3, k = lane >> 4;
+    const int col = 4 * b + k;                         // the lane's column of each 16
+    double d[NG][XG];
+    uint32_t ao[NG], xo[XG];                           // lane offsets (bytes)
+#pragma unroll
+    for (int m = 0; m < NG; ++m) ao[m] = 8u * (uint32_t)(col * nr + min(4 * m + i, nr - 1));
+#pragma unroll
+    for (int x = 0; x < XG; ++x) xo[x] = 8u * (uint32_t)((min(cc0 + 4 * x + i, r - 1) - cc0) * n + col);
+#pragma unroll
+    for (int m = 0; m < NG; ++m)
+#pragma unroll
+        for (int x = 0; x < XG; ++x) d[m][x] = 0.0;
+    const double *const xc = X + (int64_t)cc0 * n;
+    for (; q < p1; q += kSpmmWaves) {
+        const int w = pc_w[q];
+        const double *aq = A + pc_off[q], *xq = xc + pc_g[q];
+        constexpr int U = 4;                           // chunks of 16 columns in flight
+        double a[U][NG], x[U][XG];
+        auto mfmas = [&](int u) {
+#pragma unroll
+            for (int m = 0; m < NG; ++m)
+#pragma unroll
+                for (int g = 0; g < XG; ++g) d[m][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[u][m], x[u][g], d[m][g], 0, 0, 0);
+        };
+        int j0 = 0;
+        for (; j0 + 16 * U <= w; j0 += 16 * U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int jc = j0 + 16 * u;
+#pragma unroll
+                for (int m = 0; m < NG; ++m) a[u][m] = ld_off(aq + (int64_t)jc * nr, ao[m]);
+#pragma unroll
+                for (int g = 0; g < XG; ++g) x[u][g] = ld_off(xq + jc, xo[g]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) mfmas(u);
+        }
+        if (j0 < w) {                                  // the last step, its columns tested
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int jc = j0 + 16 * u;
+                const bool on = jc + col < w;
+#pragma unroll
+                for (int m = 0; m < NG; ++m) a[u][m] = on ? ld_off(aq + (int64_t)jc * nr, ao[m]) : 0.0;
+#pragma unroll
+                for (int g = 0; g < XG; ++g) x[u][g] = on ? ld_off(xq + jc, xo[g]) : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) mfmas(u);
+        }
+    }
+    // lane j + 4b + 16i holds row i, column j of block b: add the blocks
+#pragma unroll
+    for (int m = 0; m < NG; ++m)
+#pragma unroll
+        for (int x = 0; x < XG; ++x) {
+            double v = d[m][x];
+            v += __shfl_xor(v, 4, 64);
+            v += __shfl_xor(v, 8, 64);
+            if (b == 0) red[4 * m + k][4 * x + i] = v;
+        }
+}
+
+// 13 to 16 columns of X: four groups of 16 column lanes take four columns of X each, plain
+// FMAs.
+template <int MAXR, int CB>
+__device__ __forceinline__ void spmm_thin_fma(int64_t q, int64_t p1, int nr, int64_t n, int r, int cc0,
+                                          const int64_t *__restrict__ pc_off, const int64_t *__restrict__ pc_g,
+                                          const int32_t *__restrict__ pc_w, const double *__restrict__ A,
+                                          const double *__restrict__ X, double (*red)[16 * CB + 1])
+{
+    constexpr int M = 4 * CB, CL = 4, JL = 64 / CL;
     const int lane = threadIdx.x & 63, jl = lane % JL, cl = lane / JL;
     double acc[MAXR][M];
 #pragma unroll
@@ -2649,10 +2736,18 @@ __global__ __launch_bounds__(64 * kSpmmWaves, 3) void k_spmm(int32_t nc, int64_t
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t q0 = pc_rp[c] + wave, p1 = pc_rp[c + 1];
     for (int cc0 = 0; cc0 < r; cc0 += 16 * CB) {
-        if (nr <= 4 && r <= 4) spmm_thin<4, 1, 1>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
-        else if (nr <= 8 && r <= 4) spmm_thin<8, 1, 1>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
-        else if (nr <= 4) spmm_thin<4, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
-        else if (nr <= 8) spmm_thin<8, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
+        const int xg = (min(16, r - cc0) + 3) / 4;     // groups of four columns of X in this pass
+#define SPM_THIN(XG_)                                                                                        \
+        if (nr <= 4) spmm_thin<1, XG_, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);      \
+        else spmm_thin<2, XG_, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave])
+        if (nr <= 8 && xg < 4) {
+            if (xg == 1) { SPM_THIN(1); }
+            else if (xg == 2) { SPM_THIN(2); }
+            else { SPM_THIN(3); }
+        }
+        else if (nr <= 4) spmm_thin_fma<4, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
+        else if (nr <= 8) spmm_thin_fma<8, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
+#undef SPM_THIN
         else if (nr <= 16) spmm_mfma<1, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
         else spmm_mfma<2, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);
         __syncthreads();
