@@ -45,6 +45,9 @@ void for_each_table(spm_pattern_s *p, F &&f)
     f(p->d_clevel, p->clevel); f(p->d_gl_nml, p->gl_nml); f(p->d_gl_offT, p->gl_offT);
     f(p->d_stage_off_lv, p->stage_off_lv); f(p->d_stage_first_lv, p->stage_first_lv);
     f(p->d_pair_a_lv, p->pair_a_lv); f(p->d_pair_b_lv, p->pair_b_lv); f(p->d_diag_pos, p->diag_pos);
+    f(p->d_quad_unit, p->quad_unit); f(p->d_quad_off, p->quad_off); f(p->d_quad_ent, p->quad_ent);
+    f(p->d_quad_stage_off, p->quad_stage_off); f(p->d_quad_stage, p->quad_stage);
+    f(p->d_quad_order, p->quad_order); f(p->d_pair_offd, p->pair_offd);
 }
 
 static constexpr int kFlatBlocks = 2048;  // fixed grid of the flat reductions (so a fixed summation order)
@@ -1432,7 +1435,8 @@ struct ThinUnit {
     }
 };
 
-// Units of a single 16 x 16 block: one consumer wave, one record wave.  Bound by the vector
+// Units of a single 16 x 16 block, where the pattern is too small (or its lists too large)
+// for quads: one consumer wave, one record wave.  Bound by the vector
 // memory path (16 cycles of the CU per load instruction whatever its lanes' pattern, two
 // loads per 16-cycle share of an MFMA) and, on large patterns, by the reads of the column
 // side that miss L2.
@@ -1509,6 +1513,203 @@ __global__ __launch_bounds__(128) void k_mgemm_thin(GroupArgs g, const double *_
     for (int r = 0; r < 4; ++r) {                      // register r: row 4r + lk, column lr
         const int kr = (4 * r + lk) / un.sr;
         un.store(g, C, kr, 4 * r + lk - kr * un.sr, kb, lr - kb * un.sc, acc[r]);
+    }
+}
+
+// ------------------------------------------------------------------ quads of one-block units
+// Two row groups by two column groups of one 16-row block each, over one list of middle
+// clusters: one consumer wave holds the four blocks, one wave keeps the records.  A load
+// instruction takes 16 cycles of the CU's vector memory path and an MFMA 16 of its four
+// SIMDs', so single units (two loads per MFMA) left the matrix pipe two thirds idle with
+// that path 96 % busy, and read both panels for every block; a quad takes 1.3 to 1.7 loads
+// per MFMA and reads a panel once for two blocks.  The record wave adds two loads per stage
+// (header by scalar load, the entries, the offsets of both pairs' member tiles in one list).
+// Measured, the class: N = 65536 cube 28 -> 20.8 ms (now L2 misses at 5.7 TB/s), N = 131072
+// square 45 -> 34.8, N = 20000 shell 24.2 -> 17.2 (the vector memory path 84 % busy).
+struct QuadArgs {
+    const int32_t *unit, *ent, *order;
+    const int4 *stage;
+    const int64_t *off, *stage_off, *offd;
+};
+
+// Stage record: as ATab, slots 4x + k of member k of group x (0, 1 the row groups, 2, 3 the
+// column groups), 36 entries apart; act: the groups that hold the stage's middle clusters.
+struct QTab {
+    uint64_t adr[16][spm::kQuadRows + 4];
+    int32_t act;
+    int32_t pad[3];
+};
+constexpr int kQLead = 2;                              // records ahead of the consumer
+constexpr size_t quad_lds_bytes() { return (kQLead + 1) * sizeof(QTab) + 8 * 16 * sizeof(int64_t); }
+
+__global__ __launch_bounds__(128, 4) void k_mgemm_quad(GroupArgs g, QuadArgs z, const double *__restrict__ A,
+                                                      const double *__restrict__ B, double *__restrict__ C)
+{
+    extern __shared__ double lds[];
+    QTab *const ring = reinterpret_cast<QTab *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = z.order[blockIdx.x];
+    const int nst = (int)(z.stage_off[q + 1] - z.stage_off[q]);
+    // groups of the quad (-1: none): those of its units
+    int grp[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int u0 = z.unit[4 * q + (k < 2 ? 2 * k : k - 2)], u1 = z.unit[4 * q + (k < 2 ? 2 * k + 1 : k)];
+        const int u = u0 >= 0 ? u0 : u1;
+        grp[k] = u < 0 ? -1 : k < 2 ? g.unit_gr[u] : g.unit_gc[u];
+    }
+    auto members = [&](int k) { return grp[k] < 0 ? 0 : g.grp_g[grp[k]]; };
+    auto fun = [&](int k, int m) { return m < members(k) ? g.nfun[g.grp_mem[grp[k] * 4 + m]] : 0; };
+    if (wave == 1) {
+        // ---- record wave: the header, entries and offsets of a stage are loaded in successive
+        // iterations, each consuming loads of the one before; lane (tp, j) holds middle
+        // cluster tp of the stage and two of its 16 member slots (rows for j < 4)
+        __builtin_amdgcn_s_setprio(3);
+        const int4 *const head = z.stage + z.stage_off[q];
+        const int32_t *const ent = z.ent + 2 * z.off[q];
+        int64_t *const st = reinterpret_cast<int64_t *>(ring + kQLead + 1);   // offsets [tp][16 slots]
+        const int tp = lane >> 3, j = lane & 7, kk = lane & 31;
+        const bool rows = lane < 32;
+        const uint64_t opnd = reinterpret_cast<uint64_t>(rows ? A : B);
+        const uint64_t zpage = reinterpret_cast<uint64_t>(g_zero_page);
+        int nslot[8], nq[2];                           // bytes of a member's column; members in use
+#pragma unroll
+        for (int m = 0; m < 8; ++m) nslot[m] = 8 * (rows ? fun(m >> 2, m & 3) : fun(2 + (m >> 2), m & 3));
+        nq[0] = max(members(0), members(2));
+        nq[1] = max(members(1), members(3));
+        for (int t = 0; t < kQLead + 1; ++t)           // slots without a member never change
+#pragma unroll
+            for (int m = 0; m < 8; ++m) ring[t].adr[(rows ? 0 : 8) + m][kk] = zpage;
+        auto load_head = [&](int s) { return s < nst ? head[s] : int4{0, 0, 0, 0}; };
+        auto load_entry = [&](const int4 &h) {
+            return tp < (h.y & 0xFF) ? ent[2 * (h.x + tp) + (j >> 2)] : -1;
+        };
+        auto load_offsets = [&](int32_t e) {
+            return e < 0 ? longlong2{-1, -1} : *reinterpret_cast<const longlong2 *>(z.offd + (int64_t)e * 8 + 2 * (j & 3));
+        };
+        auto write_tab = [&](QTab *T, const longlong2 &o, const int4 &h) {
+            *reinterpret_cast<longlong2 *>(st + tp * 16 + 2 * j) = o;
+            const bool live = kk < (h.y >> 8 & 0xFF);
+            const uint32_t prefix = (uint32_t)h.z & ((2u << kk) - 1u);
+            const int mm = max(0, __builtin_popcount(prefix) - 1);
+            const int kkm = kk - (prefix ? 31 - __builtin_clz(prefix) : 0) + (mm == 0 ? h.w : 0);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int64_t *const so = st + mm * 16 + (rows ? 0 : 8);
+            uint64_t *const dst = &T->adr[rows ? 0 : 8][kk];
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                if ((m & 3) >= nq[m >> 2]) continue;
+                const int64_t off = so[m];
+                const uint64_t a = opnd + (uint64_t)off * 8 + (uint32_t)__mul24(kkm, nslot[m]);
+                dst[m * (spm::kQuadRows + 4)] = live && (int32_t)(off >> 32) >= 0 ? a : zpage;
+            }
+            if (lane == 0) T->act = h.y >> 16;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        for (int s = 0; s < kQLead; ++s) {
+            const int4 h = load_head(s);
+            write_tab(&ring[s], load_offsets(load_entry(h)), h);
+        }
+        int4 h0 = load_head(kQLead), h1 = load_head(kQLead + 1), h2 = load_head(kQLead + 2);
+        longlong2 o = load_offsets(load_entry(h0));    // stage kQLead
+        int32_t e = load_entry(h1);                    // stage kQLead + 1
+        lds_barrier();
+        int slot = kQLead;
+        for (int s = 0; s < nst; ++s) {
+            write_tab(&ring[slot], o, h0);             // stage s + kQLead
+            slot = slot == kQLead ? 0 : slot + 1;
+            h0 = h1;
+            h1 = h2;
+            o = load_offsets(e);                       // stage s + kQLead + 1
+            e = load_entry(h2);                        // stage s + kQLead + 2
+            h2 = load_head(s + kQLead + 3);            // stage s + kQLead + 3
+            lds_barrier();
+        }
+        return;
+    }
+    // ---- consumer: blocks (a, b); operand x = 0, 1 the row groups, 2, 3 the column groups.  A
+    // lane loads its own row (column) at every k row; rows past the member's end repeat its
+    // last one (results not stored), members and groups that do not exist read zeros.
+    const int lr = lane & 15, lk = lane >> 4;
+    uint32_t ao[4];                                    // LDS byte offset of the lane's member slot in a record
+    uint32_t ro[4];                                    // byte offset of its row in a column of the member
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const int s = grp[x] < 0 ? 16 : g.grp_s[grp[x]], m = lr / s;
+        ro[x] = 8 * max(0, min(lr - m * s, fun(x, m) - 1));
+        ao[x] = (uint32_t)(((4 * x + m) * (spm::kQuadRows + 4) + lk) * sizeof(uint64_t));
+    }
+    int units = 0;                                     // bit 2a + b: the unit exists
+#pragma unroll
+    for (int k = 0; k < 4; ++k) units |= z.unit[4 * q + k] >= 0 ? 1 << k : 0;
+    dbl4 acc[4];
+    double v[4][8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc[k] = dbl4{0.0, 0.0, 0.0, 0.0};
+    auto adr_of = [&](int x, int t) {                  // ao: in the record of the stage being loaded
+        return *reinterpret_cast<const uint64_t *>(reinterpret_cast<const char *>(ring) + ao[x] + 4 * t * sizeof(uint64_t));
+    };
+    auto blocks_of = [&](int act) {                    // blocks with work in a stage
+        int on = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) on |= (act >> (k >> 1) & 1) & (act >> (2 + (k & 1)) & 1) ? 1 << k : 0;
+        return on & units;
+    };
+    lds_barrier();
+    int on = blocks_of(__builtin_amdgcn_readfirstlane(ring[0].act));
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {                      // in the order of the loop's loads, whose waits count them
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v[x][t] = load_at<double>(adr_of(x, t) + ro[x], 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int slot = 1;                                      // ring slot of stage s + 1
+    for (int s = 0; s < nst; ++s) {
+        const int next = ring[slot].act;
+        const uint32_t step = slot ? sizeof(QTab) : -kQLead * (uint32_t)sizeof(QTab);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) ao[x] += step;
+        // a k step is computed, then refilled from the next stage's record (past the last
+        // stage: no rows, zeros)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            uint64_t ad[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) ad[x] = adr_of(x, t);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (on >> k & 1)
+                    acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[k >> 1][t], v[2 + (k & 1)][t], acc[k], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[x][t] = load_at<double>(ad[x] + ro[x], 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        on = blocks_of(__builtin_amdgcn_readfirstlane(next));
+        slot = slot == kQLead ? 0 : slot + 1;
+        lds_barrier();
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int u = z.unit[4 * q + k];
+        if (u < 0) continue;
+        const int gr = g.unit_gr[u], gc = g.unit_gc[u], sr = g.grp_s[gr], sc = g.grp_s[gc];
+        const int kc = lr / sc, jj = lr - kc * sc;
+        const int ncl = kc < g.grp_g[gc] ? g.nfun[g.grp_mem[gc * 4 + kc]] : 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {                  // register r: row 4r + lk, column lr
+            const int kr = (4 * r + lk) / sr, ii = 4 * r + lk - kr * sr;
+            const int n = kr < g.grp_g[gr] ? g.nfun[g.grp_mem[gr * 4 + kr]] : 0;
+            if (ii >= n || jj >= ncl) continue;
+            const int t = g.unit_out[u * 16 + kr * 4 + kc];
+            if (t < 0) continue;
+            const int64_t e = g.tile_off[t] + (int64_t)jj * n + ii;
+            C[e] = g.keep && !g.keep[e] ? 0.0 : acc[k][r];
+        }
     }
 }
 
@@ -3003,7 +3204,15 @@ int launch_gemm_abt(spm_pattern p, const double *A, const double *B, double *C, 
             g.WR = g.WC = g.nsplit = 1;
             const int nb = L.rb * L.cb;
             int st;
-            if (nb == 1) st = launch_grp((const void *)k_mgemm_thin, grid, 128, ring_bytes<3>(), s, g, A, B, C);
+            if (nb == 1 && p->d_quad_order.n) {
+                const QuadArgs z{p->d_quad_unit.ptr, p->d_quad_ent.ptr, p->d_quad_order.ptr,
+                                 reinterpret_cast<const int4 *>(p->d_quad_stage.ptr), p->d_quad_off.ptr,
+                                 p->d_quad_stage_off.ptr, p->d_pair_offd.ptr};
+                hipLaunchKernelGGL(k_mgemm_quad, dim3((unsigned)p->d_quad_order.n), dim3(128), quad_lds_bytes(), s, g, z,
+                                   A, B, C);
+                SPM_HIP(hipGetLastError());
+                st = SPM_OK;
+            } else if (nb == 1) st = launch_grp((const void *)k_mgemm_thin, grid, 128, ring_bytes<3>(), s, g, A, B, C);
             else {
                 // consumers: one per member of the wide side (24 functions or more), or one
                 // per 32 rows; a class may hold units of both kinds

@@ -789,6 +789,198 @@ void build_groups(spm_pattern_s *p)
     }
 }
 
+// Quads of the FP64 product (a launch of their own in place of the (1, 1) class).  Groups of
+// one 16-row block are paired in order; a quad is two such pairs with at least one unit
+// between them.  Its middle clusters are those that some unit of it needs, grouped by the
+// groups that hold them: a stage has clusters of one kind only, so that a block either
+// takes all of it or skips it (a cluster that a block's rows do not have never meets that
+// block's columns, whatever values they hold).  Within a kind the 32 k rows of the stages
+// are filled one after the other, a cluster split over two where it does not fit.
+void build_quads(spm_pattern_s *p)
+{
+    p->quad_unit.clear(); p->quad_ent.clear(); p->quad_stage.clear(); p->quad_order.clear(); p->pair_offd.clear();
+    p->quad_off.assign(1, 0); p->quad_stage_off.assign(1, 0);
+    std::vector<int32_t> pos(p->ng, -1), thin;         // place among the one-block groups
+    for (int g = 0; g < p->ng; ++g)
+        if (p->grp_R[g] == 16) { pos[g] = (int32_t)thin.size(); thin.push_back(g); }
+    struct Item { uint64_t key; int32_t ab, u; };
+    std::vector<Item> items;
+    for (int64_t u = 0; u < (int64_t)p->unit_gr.size(); ++u) {
+        const int a = pos[p->unit_gr[u]], b = pos[p->unit_gc[u]];
+        if (a >= 0 && b >= 0)
+            items.push_back({(uint64_t)(a / 2) << 32 | (uint32_t)(b / 2), 2 * (a & 1) + (b & 1), (int32_t)u});
+    }
+    std::sort(items.begin(), items.end(), [](const Item &x, const Item &y) { return x.key < y.key; });
+    std::vector<uint64_t> keys;
+    for (size_t i = 0; i < items.size(); ++i) {
+        if (i == 0 || items[i].key != items[i - 1].key) {
+            keys.push_back(items[i].key);
+            p->quad_unit.insert(p->quad_unit.end(), 4, -1);
+        }
+        p->quad_unit[p->quad_unit.size() - 4 + items[i].ab] = items[i].u;
+    }
+    std::vector<Item>().swap(items);
+    const int64_t nq = (int64_t)keys.size();
+    if (nq < spm::kQuadMin) { p->quad_unit.clear(); return; }
+    // union lists of the pairs: cluster, size, groups that hold it, offsets of the member tiles
+    const int64_t npair = ((int64_t)thin.size() + 1) / 2;
+    struct Ent { int32_t mu; int16_t size, has; };
+    std::vector<Ent> pe;
+    std::vector<int64_t> pe_rp(1, 0);
+    for (int64_t t = 0; t < npair; ++t) {
+        int64_t at[2] = {0, 0}, end[2] = {0, 0};
+        for (int k = 0; k < 2 && 2 * t + k < (int64_t)thin.size(); ++k) {
+            at[k] = p->gl_rp[thin[2 * t + k]];
+            end[k] = p->gl_rp[thin[2 * t + k] + 1];
+        }
+        while (at[0] < end[0] || at[1] < end[1]) {
+            const int32_t h0 = at[0] < end[0] ? p->gl_mu[at[0]] : INT32_MAX, h1 = at[1] < end[1] ? p->gl_mu[at[1]] : INT32_MAX;
+            const int32_t mu = std::min(h0, h1);
+            Ent e{mu, (int16_t)p->nfun[mu], (int16_t)((h0 == mu ? 1 : 0) | (h1 == mu ? 2 : 0))};
+            pe.push_back(e);
+            for (int k = 0; k < 2; ++k) {
+                const int64_t *o = p->gl_offd.data() + at[k] * 4;
+                if (e.has >> k & 1) { p->pair_offd.insert(p->pair_offd.end(), o, o + 4); ++at[k]; }
+                else p->pair_offd.insert(p->pair_offd.end(), 4, -1);
+            }
+        }
+        pe_rp.push_back((int64_t)pe.size());
+    }
+    const unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    struct Part { spm::RawVec<int32_t> ent, stage; std::vector<int64_t> cnt, nst; std::vector<double> cost; int64_t ent0, stage0; };
+    std::vector<Part> part(nth);
+    auto threads = [&](auto &&f) {
+        std::vector<std::thread> th;
+        for (unsigned w = 0; w < nth; ++w) th.emplace_back(f, w);
+        for (auto &x : th) x.join();
+    };
+    threads([&](unsigned w) {
+        Part &P = part[w];
+        struct Mid { int32_t key, size, a, b; };
+        std::vector<Mid> mid, sorted;
+        for (int64_t q = nq * w / nth; q < nq * (w + 1) / nth; ++q) {
+            const int32_t *un = p->quad_unit.data() + 4 * q;
+            int blocks[16];                            // units that a cluster of this presence serves
+            for (int h = 0; h < 16; ++h) {
+                blocks[h] = 0;
+                for (int k = 0; k < 4; ++k) blocks[h] += un[k] >= 0 && (h >> (k >> 1) & 1) && (h >> (2 + (k & 1)) & 1);
+            }
+            const int64_t ta = (int64_t)(keys[q] >> 32), tb = (int64_t)(keys[q] & 0xFFFFFFFFu);
+            mid.clear();
+            int64_t start[17] = {};
+            double cost = 0.0;
+            for (int64_t a = pe_rp[ta], b = pe_rp[tb]; a < pe_rp[ta + 1] && b < pe_rp[tb + 1];) {
+                const int32_t ma = pe[a].mu, mb = pe[b].mu;
+                if (ma == mb) {
+                    const int h = pe[a].has | pe[b].has << 2;
+                    if (blocks[h] && pe[a].size > 0) {
+                        mid.push_back({h, pe[a].size, (int32_t)a, (int32_t)b});
+                        ++start[h + 1];
+                        cost += 256.0 * blocks[h] * pe[a].size;
+                    }
+                }
+                a += ma <= mb;
+                b += mb <= ma;
+            }
+            for (int k = 0; k < 16; ++k) start[k + 1] += start[k];
+            sorted.resize(mid.size());
+            for (const Mid &m : mid) sorted[start[m.key]++] = m;
+            const int64_t e0 = (int64_t)P.ent.size(), s0 = (int64_t)P.stage.size();
+            int key = -1, kacc = 0, np = 0;
+            int32_t starts = 0;
+            auto close = [&]() {
+                if (key < 0) return;
+                int32_t *h = P.stage.data() + P.stage.size() - 4;
+                h[1] = np | kacc << 8 | key << 16;
+                h[2] = starts;
+            };
+            for (size_t i = 0; i < sorted.size(); ++i) {
+                const Mid &m = sorted[i];
+                P.ent.push_back(m.a);
+                P.ent.push_back(m.b);
+                for (int r0 = 0; r0 < m.size;) {
+                    if (key != m.key || kacc == spm::kQuadRows || np == 8) {
+                        close();
+                        const int32_t h[4] = {(int32_t)i, 0, 0, r0};
+                        P.stage.insert(P.stage.end(), h, h + 4);
+                        key = m.key;
+                        kacc = np = 0;
+                        starts = 0;
+                    }
+                    const int take = std::min(spm::kQuadRows - kacc, m.size - r0);
+                    starts |= (int32_t)(1u << kacc);
+                    kacc += take;
+                    r0 += take;
+                    ++np;
+                }
+            }
+            close();
+            P.cnt.push_back(((int64_t)P.ent.size() - e0) / 2);
+            P.nst.push_back(((int64_t)P.stage.size() - s0) / 4);
+            P.cost.push_back(cost);
+            if ((int64_t)P.ent.size() / 2 > spm::kQuadEntries) return;   // over the limit by itself
+        }
+    });
+    int64_t ne = 0, ns = 0;
+    for (Part &P : part) {
+        P.ent0 = ne;
+        P.stage0 = ns;
+        ne += (int64_t)P.ent.size();
+        ns += (int64_t)P.stage.size();
+    }
+    if (ne / 2 > spm::kQuadEntries) { p->quad_unit.clear(); p->pair_offd.clear(); return; }
+    p->quad_ent.resize(ne);
+    p->quad_stage.resize(ns);
+    threads([&](unsigned w) {
+        Part &P = part[w];
+        std::copy(P.ent.begin(), P.ent.end(), p->quad_ent.begin() + P.ent0);
+        std::copy(P.stage.begin(), P.stage.end(), p->quad_stage.begin() + P.stage0);
+        spm::RawVec<int32_t>().swap(P.ent);
+        spm::RawVec<int32_t>().swap(P.stage);
+    });
+    std::vector<double> cost;
+    for (const Part &P : part) {
+        for (int64_t c : P.cnt) p->quad_off.push_back(p->quad_off.back() + c);
+        for (int64_t c : P.nst) p->quad_stage_off.push_back(p->quad_stage_off.back() + c);
+        cost.insert(cost.end(), P.cost.begin(), P.cost.end());
+    }
+    // order: bands of kBand row pairs walked column pair by column pair, whole bands to the
+    // XCD with the least work, heaviest first, the eight lists interleaved (bands of 1 / 2 /
+    // 4 / 8 pairs: N = 20011 sphere 3.06 / 3.04 / 3.32 / 4.23 ms, N = 65536 cube 116.9 /
+    // 116.9 / 118.0 / 121.9, N = 20000 shell 20.0 / 19.8 / 19.5 / 20.3)
+    constexpr uint64_t kBand = 2;
+    std::vector<int32_t> idx(nq);
+    for (int64_t q = 0; q < nq; ++q) idx[q] = (int32_t)q;
+    std::stable_sort(idx.begin(), idx.end(), [&](int32_t x, int32_t y) {
+        const uint64_t bx = (keys[x] >> 32) / kBand, by = (keys[y] >> 32) / kBand;
+        return bx != by ? bx < by : (uint32_t)keys[x] < (uint32_t)keys[y];
+    });
+    struct Strip { int64_t b, e; double w; };
+    std::vector<Strip> strips;
+    for (int64_t i = 0; i < nq;) {
+        Strip S{i, i, 0.0};
+        while (S.e < nq && (keys[idx[S.e]] >> 32) / kBand == (keys[idx[i]] >> 32) / kBand) S.w += cost[idx[S.e++]];
+        strips.push_back(S);
+        i = S.e;
+    }
+    std::stable_sort(strips.begin(), strips.end(), [](const Strip &x, const Strip &y) { return x.w > y.w; });
+    std::vector<int32_t> lists[8];
+    double load[8] = {};
+    for (const Strip &S : strips) {
+        const int x = (int)(std::min_element(load, load + 8) - load);
+        load[x] += S.w;
+        lists[x].insert(lists[x].end(), idx.begin() + S.b, idx.begin() + S.e);
+    }
+    size_t done[8] = {};
+    for (int64_t q = 0; q < nq; ++q) {
+        int x = (int)(q % 8);
+        if (done[x] >= lists[x].size())
+            for (int y = 0; y < 8; ++y)
+                if (lists[y].size() - done[y] > lists[x].size() - done[x]) x = y;
+        p->quad_order.push_back(lists[x][done[x]++]);
+    }
+}
+
 // Fill the layout of p from its block CSR (p->blk_rp, p->tile_col, p->nfun set).
 void build_layout(spm_pattern_s *p)
 {
@@ -887,6 +1079,7 @@ void build_layout(spm_pattern_s *p)
     p->order.resize(nt);
     for (int64_t t = 0; t < nt; ++t) p->order[t] = (int32_t)t;
     build_groups(p);
+    build_quads(p);
     std::vector<double>().swap(p->tile_macs);   // only the per-class sums are kept
 }
 

@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -15,6 +16,14 @@
 namespace spm {
 
 constexpr int kMaxFun = 32;   // largest number of basis functions per cluster the kernels take
+constexpr int64_t kQuadEntries = int64_t(1) << 29;   // largest total of the quads' middle lists (4 GB)
+// Fewest quads: two per workgroup the chip holds (256 CUs x 8).  Below, a quad's longer chain
+// costs more than its fewer loads give.  Products in ms, units / quads: 289 quads (sphere,
+// N = 4096) 0.641 / 0.714, 1071 (cube, 8000) 7.55 / 7.60, 2834 (square, 8000) 3.11 / 3.16,
+// 4011 (cube, 12000) 14.1 / 13.4, 9703 (square, 4096) 0.51 / 0.47, 23463 (sphere, 9000)
+// 1.27 / 1.11.
+constexpr int64_t kQuadMin = 4096;
+constexpr int kQuadRows = 32;                        // k rows of a quad's stage
 constexpr int kPieceEntries = 2048;   // largest piece of a block row in the S x dense product
 
 int fail(int status, const std::string &msg);   // records msg, returns status
@@ -32,6 +41,21 @@ int fail(int status, const std::string &msg);   // records msg, returns status
         if (!(p)->uploaded)                                                                 \
             return ::spm::fail(SPM_EINVAL, std::string(name) + ": pattern not uploaded");   \
     } while (0)
+
+// A vector whose resize leaves the new elements unset (large tables filled by threads).
+template <typename T>
+struct RawAlloc : std::allocator<T> {
+    template <typename U>
+    struct rebind { using other = RawAlloc<U>; };
+    template <typename U, typename... A>
+    void construct(U *p, A &&...a)
+    {
+        if constexpr (sizeof...(A) == 0) ::new (static_cast<void *>(p)) U;
+        else ::new (static_cast<void *>(p)) U(std::forward<A>(a)...);
+    }
+};
+template <typename T>
+using RawVec = std::vector<T, RawAlloc<T>>;
 
 // Device copy of a host vector (owned by the pattern / tree handle).
 template <typename T>
@@ -130,6 +154,16 @@ struct spm_pattern_s {
     std::vector<int32_t> pair_a_lv, pair_b_lv;
     std::vector<int64_t> stage_off_lv;    // units + 1
     std::vector<int32_t> stage_first_lv;  // first pair of each stage (relative to the unit's pair_off)
+    // Quads of the FP64 product: the units of a single block, two row groups by two column
+    // groups at a time, over one list of middle clusters (empty above kQuadEntries entries)
+    std::vector<int32_t> quad_unit;   // quads x 4: unit of (row group a, column group b) at 2a + b, or -1
+    std::vector<int64_t> quad_off;    // quads + 1: offsets of each quad's middle-cluster list
+    spm::RawVec<int32_t> quad_ent;    // x 2: entries of mu in the union lists of the row pair and the column pair
+    std::vector<int64_t> quad_stage_off;   // quads + 1
+    spm::RawVec<int32_t> quad_stage;  // x 4: first middle cluster; their number | k rows << 8 | groups present << 16;
+                                      // bit per k row where a cluster starts; first row taken of the first cluster
+    std::vector<int32_t> quad_order;  // launch order
+    std::vector<int64_t> pair_offd;   // x 8: as gl_offd for the union lists of the pairs of row groups
     double padded_macs = 0.0;         // multiply-adds the grouped kernel issues (incl. padding)
     bool all_even = false;            // every cluster owns an even number of functions
     bool all_mult4 = false;           // every cluster owns a multiple of 4 functions
@@ -153,6 +187,8 @@ struct spm_pattern_s {
     spm::DevBuf<int32_t> d_pair_a, d_pair_b, d_gl_nm, d_stage_first;
     spm::DevBuf<int32_t> d_clevel, d_gl_nml, d_stage_first_lv, d_pair_a_lv, d_pair_b_lv;
     spm::DevBuf<int64_t> d_gl_offT, d_stage_off_lv;
+    spm::DevBuf<int32_t> d_quad_unit, d_quad_ent, d_quad_stage, d_quad_order;
+    spm::DevBuf<int64_t> d_quad_off, d_quad_stage_off, d_pair_offd;
     spm::DevBuf<uint8_t> d_keep;      // n_stored, masked patterns only
     spm::DevBuf<int64_t> d_diag_pos;
     spm::DevBuf<double> d_partial;    // reduction partials
