@@ -1089,7 +1089,7 @@ constexpr int vmcnt_at_most(int n) { return (n & 15) | (n >> 4) << 14 | 0x70 | 0
 
 // A and B: the operands' addresses, ES bytes per value (ATab records; unused for OzTab).
 // CW: bytes per lane of the copies of the shared side (4 when a cluster size is odd).
-template <int LEAD, bool SHARE, int ES, typename Rec = ATab, int CW = 16>
+template <int LEAD, bool SHARE, int ES, typename Rec = ATab, int CW = 16, bool ACT = SHARE>
 __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *lds, Rec *ring, int lane,
                                 const SharedSide &sh, const void *A, const void *B)
 {
@@ -1194,7 +1194,7 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
                 const uint64_t a = opnd + (uint64_t)o * ES + (uint32_t)__mul24(kkm, nslot[q]);
                 const bool on = live && (int32_t)(o >> 32) >= 0;
                 dst[q * (kKS + 4)] = on ? a : zpage;
-                if constexpr (SHARE) {
+                if constexpr (ACT) {
                     const uint64_t b = __builtin_amdgcn_ballot_w64(on);
                     act |= ((uint32_t)b != 0 ? 1 << q : 0) | ((b >> 32) != 0 ? 16 << q : 0);
                 }
@@ -1843,13 +1843,27 @@ __global__ __launch_bounds__(320, 6) void k_mgemm_side(GroupArgs g, const double
 constexpr int kHS = 16;      // k rows per panel buffer
 constexpr int kWX = 128;     // panel row stride
 constexpr int kWB = 7;       // largest number of blocks a side
-constexpr size_t wide_lds_bytes() { return 2 * sizeof(double) * kHS * 2 * kWX + 2 * sizeof(ATab); }
+// F32ACC (E = float, every size a multiple of four): a lane gathers four rows, so a wave's
+// instruction takes two k rows, k and k + 4 of the half; such a pair is followed by 16
+// floats, so that the four k rows of an MFMA lie in different banks.  The FP32 sums of a
+// stage go into the FP64 accumulators of the blocks that had work in it.  Measured, 22
+// products of N = 16384 cube's 7 x 7 units: 112 ms register-direct (16-byte loads whose lane
+// quads read four columns, two waves per SIMD at 229 VGPRs), 51.9 ms from the panels.
+template <typename E>
+constexpr int wide_panel() { return sizeof(E) == 8 ? kHS * kWX : kHS / 2 * (2 * kWX + 16); }
+template <typename E>
+constexpr size_t wide_lds_bytes() { return 2 * sizeof(E) * 2 * wide_panel<E>() + 2 * sizeof(ATab); }
 
-__global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double *__restrict__ A,
-                                                       const double *__restrict__ B, double *__restrict__ C)
+template <typename E>
+__global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const E *__restrict__ A, const E *__restrict__ B,
+                                                       E *__restrict__ C)
 {
-    extern __shared__ double lds[];
-    constexpr int PD = kHS * 2 * kWX;                  // doubles of one buffer (A rows, then B columns)
+    extern __shared__ double lds_raw[];
+    E *const lds = reinterpret_cast<E *>(lds_raw);
+    constexpr bool F64 = sizeof(E) == 8;
+    constexpr int ES = sizeof(E), LR = 16 / ES;        // rows of a lane's load
+    constexpr int PD = 2 * wide_panel<E>();            // elements of one buffer (A rows, then B columns)
+    constexpr int LS = F64 ? kWX : 2 * kWX + 16;       // from an MFMA's k row to the next
     ATab *const tab = reinterpret_cast<ATab *>(lds + 2 * PD);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1864,26 +1878,27 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double
     const int nc0 = fun(gc, ngc, 0), nc1 = fun(gc, ngc, 1), nc2 = fun(gc, ngc, 2), nc3 = fun(gc, ngc, 3);
     const int64_t s0 = g.stage_off[u], p0 = g.pair_off[u];
     const int nst = (int)(g.stage_off[u + 1] - s0);
-    // this lane's row pair of either panel: its member (past the group's end: a slot without
+    // this lane's rows of either panel: their member (past the group's end: a slot without
     // tiles, so zeros) and byte offset in the member's column (past the member's end its
-    // last pair again; those results are not stored)
-    const int ka = min(2 * lane / sr, 3), kb = min(2 * lane / sc, 3);
-    const uint32_t ba = 8 * max(0, min(2 * lane - ka * sr, sel4(ka, nr0, nr1, nr2, nr3) - 2));
-    const uint32_t bb = 8 * max(0, min(2 * lane - kb * sc, sel4(kb, nc0, nc1, nc2, nc3) - 2));
-    auto dma16 = [&](uint64_t src, double *dst) {
+    // last ones again; those results are not stored)
+    const int pl = F64 ? lane : lane & 31, k4 = F64 ? 0 : lane >> 5 << 2;
+    const int ka = min(LR * pl / sr, 3), kb = min(LR * pl / sc, 3);
+    const uint32_t ba = ES * max(0, min(LR * pl - ka * sr, sel4(ka, nr0, nr1, nr2, nr3) - LR));
+    const uint32_t bb = ES * max(0, min(LR * pl - kb * sc, sel4(kb, nc0, nc1, nc2, nc3) - LR));
+    auto dma16 = [&](uint64_t src, E *dst) {
         __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(src),
                                          (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
     };
     auto half_rows = [](int ks, int h) { return max(0, min(ks - kHS * h, kHS)); };
-    // rows wave and wave + 8 of the panels of half h (whole k steps; rows past the stage's
-    // last cluster are zeros)
-    auto gather = [&](const ATab *T, int h, int rows, double *buf) {
+    // rows wave and wave + 8 of the panels of half h (E = float: its rows 8 (wave / 4) +
+    // wave % 4 and that + 4); whole k steps, rows past the stage's last cluster are zeros
+    auto gather = [&](const ATab *T, int h, int rows, E *buf) {
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int k = wave + 8 * r;
+        for (int r = 0; r < (F64 ? 2 : 1); ++r) {
+            const int k = F64 ? wave + 8 * r : wave + (wave & 4), at = F64 ? k : wave;
             if (k < ((rows + 3) & ~3)) {
-                dma16(T->adr[ka][kHS * h + k] + ba, buf + k * kWX);
-                dma16(T->adr[4 + kb][kHS * h + k] + bb, buf + (kHS + k) * kWX);
+                dma16(T->adr[ka][kHS * h + k + k4] + ba, buf + at * LS);
+                dma16(T->adr[4 + kb][kHS * h + k + k4] + bb, buf + PD / 2 + at * LS);
             }
         }
     };
@@ -1947,7 +1962,7 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double
                 const int sl = (rows ? 0 : 4) + q;
                 const int64_t o = __shfl(t_off, mm * 8 + sl);
                 const bool on = live && o >= 0;
-                T->adr[sl][kk] = on ? opnd + (uint64_t)o * 8 + (uint32_t)(kkm * nslot[q] * 8) : zpage;
+                T->adr[sl][kk] = on ? opnd + (uint64_t)o * ES + (uint32_t)(kkm * nslot[q] * ES) : zpage;
                 const uint64_t b = __builtin_amdgcn_ballot_w64(on);
                 act0 |= ((b & 0xFFFFull) != 0 ? 1 << q : 0) | ((b >> 32 & 0xFFFFull) != 0 ? 16 << q : 0);
                 act1 |= ((b >> 16 & 0xFFFFull) != 0 ? 1 << q : 0) | ((b >> 48) != 0 ? 16 << q : 0);
@@ -2012,27 +2027,33 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double
         const int c0 = 16 * j / sc, c1 = min((16 * j + 15) / sc, 3);
         bmask[j] = c0 > 3 || j >= g.CB ? 0 : (((2 << c1) - 1) & ~((1 << c0) - 1)) << 4;
     }
-    const double *const fa0 = lds + lk * kWX + 16 * wave + lr, *const fb0 = lds + (kHS + lk) * kWX + lr;
+    typedef float flt4 __attribute__((ext_vector_type(4)));
+    flt4 a32[F64 ? 1 : kWB];                           // FP32 sums of the stage
+    const E *const fa0 = lds + lk * LS + 16 * wave + lr, *const fb0 = lds + PD / 2 + lk * LS + lr;
+    auto step = [](int t) { return F64 ? 4 * t * kWX : (t >> 1) * 4 * LS + (t & 1) * kWX; };
     auto compute = [&](int buf, int rows, int act) {
-        const double *pa = fa0 + buf * PD, *pb = fb0 + buf * PD;
+        const E *pa = fa0 + buf * PD, *pb = fb0 + buf * PD;
         if (!active || (act & amask) == 0) return;
-        double fa[4], nb[4];
+        E fa[4], nb[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) fa[t] = pa[4 * t * kWX];
+        for (int t = 0; t < 4; ++t) fa[t] = pa[step(t)];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) nb[t] = pb[4 * t * kWX];
+        for (int t = 0; t < 4; ++t) nb[t] = pb[step(t)];
 #pragma unroll
         for (int j = 0; j < kWB; ++j) {
-            double fb[4];
+            E fb[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) fb[t] = nb[t];
             if (j + 1 < kWB)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) nb[t] = pb[4 * t * kWX + 16 * (j + 1)];
+                for (int t = 0; t < 4; ++t) nb[t] = pb[step(t) + 16 * (j + 1)];
             if ((act & bmask[j]) != 0) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    if (4 * t < rows) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[t], fb[t], acc[j], 0, 0, 0);
+                    if (4 * t < rows) {
+                        if constexpr (F64) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[t], fb[t], acc[j], 0, 0, 0);
+                        else a32[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[t], fb[t], a32[j], 0, 0, 0);
+                    }
             }
         }
     };
@@ -2046,11 +2067,23 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double
         const int act1 = __builtin_amdgcn_readfirstlane(T->act_half[1]);
         const int r0 = half_rows(ks, 0), r1 = half_rows(ks, 1);
         gather(T, 1, r1, lds + PD);
+        if constexpr (!F64)
+#pragma unroll
+            for (int j = 0; j < kWB; ++j) a32[j] = flt4{0.f, 0.f, 0.f, 0.f};
         compute(0, r0, act0);
         sync();                                        // second half landed
         ks = __builtin_amdgcn_readfirstlane(T1->ks);
         gather(T1, 0, half_rows(ks, 0), lds);
         if (r1 > 0) compute(1, r1, act1);
+        if constexpr (!F64) {
+            const int act = act0 | act1;
+            if (!active || (act & amask) == 0) continue;
+#pragma unroll
+            for (int j = 0; j < kWB; ++j)
+                if ((act & bmask[j]) != 0)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[j][r] += (double)a32[j][r];
+        }
     }
     __builtin_amdgcn_s_waitcnt(0);
     if (!active) return;
@@ -2062,14 +2095,14 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double
         if (kc >= ngc || jj >= sel4(kc & 3, nc0, nc1, nc2, nc3)) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int row = 16 * wave + 4 * r + lk;
+            const int row = 16 * wave + (F64 ? 4 * r + lk : 4 * lk + r);
             const int kr = row / sr, ii = row - kr * sr;
             if (kr >= ngr) continue;
             const int nr = sel4(kr & 3, nr0, nr1, nr2, nr3);
             const int t = g.unit_out[u * 16 + kr * 4 + kc];
             if (t >= 0 && ii < nr) {
                 const int64_t e = g.tile_off[t] + (int64_t)jj * nr + ii;
-                C[e] = g.keep && !g.keep[e] ? 0.0 : acc[j][r];
+                C[e] = g.keep && !g.keep[e] ? E(0) : (E)acc[j][r];
             }
         }
     }
@@ -2078,7 +2111,9 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const double
 // ---------------------------------------------------------------- FP32-accumulate product
 // F32ACC: the same unit schedule with FP32 operands and v_mfma_f32_16x16x4f32.  Each
 // stage's MFMA sums (FP32, 32 k rows) are added into FP64 accumulators; the result is
-// rounded to FP32 once.  Register-direct for every unit class: consumer wave w owns
+// rounded to FP32 once.  Where every cluster size is a multiple of four, units of 5 to 7
+// blocks a side run on k_mgemm_wide and those of one block by 4 to 8 on k_mgemm_f32side;
+// the others are register-direct here: consumer wave w owns
 // block row w (all column blocks, MC >= CB) when the unit has several block rows, else
 // column block w; the last wave keeps the records.  QUAD (every cluster size a multiple
 // of 4): a 16-byte load gives rows 4m .. 4m+3 of one k column; lane 4m + q loads it at
@@ -2272,6 +2307,117 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_f32acc(GroupArgs g, const 
             }
         }
     }
+}
+
+// One block on one side, 4 to 8 on the other, every cluster size a multiple of four: a
+// consumer wave owns 64 positions of the wider side, four adjacent ones a lane, so that one
+// 16-byte load per k step, whose lane quads read 64 bytes of a column, gives the operands
+// of four MFMAs (block c: the positions 4 l + c) with nothing to transpose; the single block
+// is one 4-byte load.  A stage's fragments are loaded while the stage before is computed.
+// Bound by the vector memory path (two loads for four MFMAs) and the additions in double
+// precision.  Measured, 22 products of N = 16384 cube's 1 x 7 and 7 x 1 units: 108.9 ms with a
+// block per wave and transposed 16-byte loads (111.8 with two blocks, 108.3 with loads a
+// whole stage ahead), 89.4 ms here.
+constexpr int kF32SideMin = 4;                         // blocks: with three a quarter of a wave's work is padding
+
+__global__ __launch_bounds__(192, 4) void k_mgemm_f32side(GroupArgs g, const float *__restrict__ A,
+                                                         const float *__restrict__ B, float *__restrict__ C)
+{
+    typedef float flt4 __attribute__((ext_vector_type(4)));
+    extern __shared__ double lds[];
+    ATab *ring = reinterpret_cast<ATab *>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t uidx = blockIdx.x;
+    if (uidx >= g.count) return;
+    const int u = g.unit_order[g.first + uidx];
+    const int gr = g.unit_gr[u], gc = g.unit_gc[u];
+    const int sr = g.grp_s[gr], sc = g.grp_s[gc];
+    const int ngr = g.grp_g[gr], ngc = g.grp_g[gc];
+    auto fun = [&](int gg, int ng, int q) { return q < ng ? g.nfun[g.grp_mem[gg * 4 + q]] : 0; };
+    const int nr0 = fun(gr, ngr, 0), nr1 = fun(gr, ngr, 1), nr2 = fun(gr, ngr, 2), nr3 = fun(gr, ngr, 3);
+    const int nc0 = fun(gc, ngc, 0), nc1 = fun(gc, ngc, 1), nc2 = fun(gc, ngc, 2), nc3 = fun(gc, ngc, 3);
+    const bool own_rows = g.RB > 1;
+    const int64_t s0 = g.stage_off[u], p0 = g.pair_off[u];
+    const int nst = (int)(g.stage_off[u + 1] - s0), npairs = (int)(g.pair_off[u + 1] - p0);
+    if (wave == 2) {
+        const UnitInfo ui{s0, p0, nst, npairs, ngr, ngc, nr0, nr1, nr2, nr3, nc0, nc1, nc2, nc3};
+        record_producer<2, false, 4, ATab, 16, true>(g, ui, lds, ring, lane, SharedSide{}, A, B);
+        return;
+    }
+    if (64 * wave >= 16 * (own_rows ? g.RB : g.CB)) {
+        lds_barrier();
+        for (int s = 0; s < nst; ++s) lds_barrier();
+        return;
+    }
+    const int lr = lane & 15, lk = lane >> 4;
+    auto size_of = [&](bool rows, int k) { return rows ? sel4(k, nr0, nr1, nr2, nr3) : sel4(k, nc0, nc1, nc2, nc3); };
+    // the lane's four positions of its own side and its position of the single block; past a
+    // member's end its last ones again (results not stored)
+    const int so = own_rows ? sr : sc, ss = own_rows ? sc : sr;
+    const int po = 64 * wave + 4 * lr, ko = min(po / so, 3), kx = min(lr / ss, 3);
+    const uint32_t bo = 4 * max(0, min(po - ko * so, size_of(own_rows, ko) - 4));
+    const uint32_t bs = 4 * max(0, min(lr - kx * ss, size_of(!own_rows, kx) - 1));
+    const int slot_o = (own_rows ? 0 : 4) + ko, slot_s = (own_rows ? 4 : 0) + kx;
+    // members of the wave's 64 positions (bits of act): a stage without a tile of theirs adds only zeros
+    const int m0 = min(64 * wave / so, 4), m1 = min((64 * wave + 63) / so, 3);
+    const int omask = (((2 << m1) - 1) & ~((1 << m0) - 1)) << (own_rows ? 0 : 4);
+    dbl4 acc[4];
+    flt4 vo[8];
+    float vs[8];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = dbl4{0.0, 0.0, 0.0, 0.0};
+    lds_barrier();
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {                      // in the order of the loop's loads, whose waits count them
+        vo[t] = load_at<flt4>(ring[0].adr[slot_o][4 * t + lk] + bo, 0);
+        vs[t] = load_at<float>(ring[0].adr[slot_s][4 * t + lk] + bs, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    int act = __builtin_amdgcn_readfirstlane(ring[0].act & omask);
+    int slot = 0;                                      // ring slot of stage s
+    for (int s = 0; s < nst; ++s) {
+        slot = slot == 2 ? 0 : slot + 1;
+        const ATab *T = &ring[slot];                   // stage s + 1 (past the last: no rows, zeros)
+        const int next = T->act & omask;
+        flt4 a32[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a32[c] = flt4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint64_t ao = T->adr[slot_o][4 * t + lk], as = T->adr[slot_s][4 * t + lk];
+            __builtin_amdgcn_sched_barrier(0);
+            if (act != 0)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a32[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vs[t], vo[t][c], a32[c], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            vo[t] = load_at<flt4>(ao + bo, 0);
+            vs[t] = load_at<float>(as + bs, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (act != 0)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[c][r] += (double)a32[c][r];
+        act = __builtin_amdgcn_readfirstlane(next);
+        lds_barrier();
+    }
+    // register r of lane l: position 4 (l / 16) + r of the single block, 4 (l % 16) + c of the wave's 64
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int row = own_rows ? po + c : 4 * lk + r, col = own_rows ? 4 * lk + r : po + c;
+            const int kr = row / sr, ii = row - kr * sr, kc = col / sc, jj = col - kc * sc;
+            if (kr >= ngr || kc >= ngc) continue;
+            const int n = size_of(true, kr);
+            const int t = g.unit_out[u * 16 + kr * 4 + kc];
+            if (t >= 0 && ii < n && jj < size_of(false, kc)) {
+                const int64_t e = g.tile_off[t] + (int64_t)jj * n + ii;
+                C[e] = g.keep && !g.keep[e] ? 0.f : (float)acc[c][r];
+            }
+        }
 }
 
 // ---------------------------------------------------------------- split-precision product on matrix cores
@@ -3225,7 +3371,7 @@ int launch_gemm_abt(spm_pattern p, const double *A, const double *B, double *C, 
         }
         if (wide && L.rb >= 5 && L.rb <= kWB && L.cb >= 5 && L.cb <= kWB) {
             g.WR = g.WC = g.nsplit = 1;
-            int st = launch_grp((const void *)k_mgemm_wide, grid, 512, wide_lds_bytes(), s, g, A, B, C);
+            int st = launch_grp((const void *)k_mgemm_wide<double>, grid, 512, wide_lds_bytes<double>(), s, g, A, B, C);
             if (st) return st;
             continue;
         }
@@ -3357,9 +3503,17 @@ int gemm_f32acc_ws(spm_pattern p, const float *A, int ta, const float *B, int tb
         const dim3 grid((unsigned)L.count);
         const void *k;
         int threads = 512;
-        if (L.rb * L.cb == 1) {
+        size_t lds = ring;
+        // loads of four rows need every size a multiple of four (lw == 4)
+        if (lw == 4 && L.rb >= 5 && L.rb <= kWB && L.cb >= 5 && L.cb <= kWB) {
+            k = (const void *)k_mgemm_wide<float>;
+            lds = wide_lds_bytes<float>();
+        } else if (L.rb * L.cb == 1) {
             k = lw == 4 ? (const void *)k_mgemm_f32acc<2, 1, 4> : lw == 2 ? (const void *)k_mgemm_f32acc<2, 1, 2> : (const void *)k_mgemm_f32acc<2, 1, 1>;
             threads = 128;
+        } else if (lw == 4 && std::min(L.rb, L.cb) == 1 && std::max(L.rb, L.cb) >= kF32SideMin) {
+            k = (const void *)k_mgemm_f32side;
+            threads = 192;
         } else if (L.rb == 1 || L.cb == 1) {
             // one block per consumer wave (block rows or block columns)
             k = lw == 4 ? (const void *)k_mgemm_f32acc<8, 1, 4> : lw == 2 ? (const void *)k_mgemm_f32acc<8, 1, 2> : (const void *)k_mgemm_f32acc<8, 1, 1>;
@@ -3373,7 +3527,7 @@ int gemm_f32acc_ws(spm_pattern p, const float *A, int ta, const float *B, int tb
         // a unit of one block row (RB == 1) with several column blocks gives each wave one
         // block; with several block rows each wave takes a row of blocks
         if (L.rb == 1 && L.cb > 1) g.RB = 1;
-        st = launch_grp(k, grid, threads, ring, s, g, reinterpret_cast<const double *>(Ap),
+        st = launch_grp(k, grid, threads, lds, s, g, reinterpret_cast<const double *>(Ap),
                         reinterpret_cast<const double *>(Bp), reinterpret_cast<double *>(C));
     }
     return st;
