@@ -4,6 +4,7 @@
 // Built with -ffp-contract=off: the admissibility test and the tree split compare
 // floating-point values, and every operation there rounds on its own.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -821,7 +822,15 @@ void build_quads(spm_pattern_s *p)
     }
     std::vector<Item>().swap(items);
     const int64_t nq = (int64_t)keys.size();
-    if (nq < spm::kQuadMin) { p->quad_unit.clear(); return; }
+    // a quad's list holds at least the middle clusters of its longest unit
+    int64_t least = 0;
+    for (int64_t q = 0; q < nq; ++q) {
+        int64_t n = 0;
+        for (int k = 0; k < 4; ++k)
+            if (const int32_t u = p->quad_unit[4 * q + k]; u >= 0) n = std::max(n, p->pair_off[u + 1] - p->pair_off[u]);
+        least += n;
+    }
+    if (nq < spm::kQuadMin || least > spm::kQuadEntries) { p->quad_unit.clear(); return; }
     // union lists of the pairs: cluster, size, groups that hold it, offsets of the member tiles
     const int64_t npair = ((int64_t)thin.size() + 1) / 2;
     struct Ent { int32_t mu; int16_t size, has; };
@@ -849,9 +858,13 @@ void build_quads(spm_pattern_s *p)
     const unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     struct Part { spm::RawVec<int32_t> ent, stage; std::vector<int64_t> cnt, nst; std::vector<double> cost; int64_t ent0, stage0; };
     std::vector<Part> part(nth);
+    std::atomic<int64_t> listed{0};                    // entries of all threads
     auto threads = [&](auto &&f) {
         std::vector<std::thread> th;
-        for (unsigned w = 0; w < nth; ++w) th.emplace_back(f, w);
+        for (unsigned w = 0; w < nth; ++w)
+            th.emplace_back([&, w]() {
+                try { f(w); } catch (const std::bad_alloc &) { listed = spm::kQuadEntries + 1; }   // no quads then
+            });
         for (auto &x : th) x.join();
     };
     threads([&](unsigned w) {
@@ -918,9 +931,10 @@ void build_quads(spm_pattern_s *p)
             P.cnt.push_back(((int64_t)P.ent.size() - e0) / 2);
             P.nst.push_back(((int64_t)P.stage.size() - s0) / 4);
             P.cost.push_back(cost);
-            if ((int64_t)P.ent.size() / 2 > spm::kQuadEntries) return;   // over the limit by itself
+            if ((listed += ((int64_t)P.ent.size() - e0) / 2) > spm::kQuadEntries) return;
         }
     });
+    if (listed > spm::kQuadEntries) { p->quad_unit.clear(); p->pair_offd.clear(); return; }
     int64_t ne = 0, ns = 0;
     for (Part &P : part) {
         P.ent0 = ne;
@@ -928,7 +942,6 @@ void build_quads(spm_pattern_s *p)
         ne += (int64_t)P.ent.size();
         ns += (int64_t)P.stage.size();
     }
-    if (ne / 2 > spm::kQuadEntries) { p->quad_unit.clear(); p->pair_offd.clear(); return; }
     p->quad_ent.resize(ne);
     p->quad_stage.resize(ns);
     threads([&](unsigned w) {
