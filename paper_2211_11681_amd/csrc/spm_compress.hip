@@ -224,12 +224,16 @@ __device__ __forceinline__ void subtree_transform(const StageTab &T, int64_t u, 
 }
 
 // Kernel block of the rows of subtree sub0 + blockIdx.y and the columns of subtree
-// blockIdx.x (both of stage 1), transformed on both sides, to rows p0 .. of W.  Bound by the
-// vector unit (distance, square root, exponential) and the matrix products, which exclude
-// each other: about 7 and 8 ms of N = 65536; one write of W.
+// blockIdx.x (both of stage 1), its columns transformed, to rows p0 .. of W; the rows as well
+// (both) where the tree has no later column stage.  With one, the rows wait for it: a column
+// stage after them would round row scaling coefficients, larger than the kernel values by
+// the root of their points' number, which shows where fine rows meet coarse columns
+// (million-point square: 1.4e-12 of the sampled entries' norm, 0.8e-12 in this order).
+// Bound by the vector unit (distance, square root, exponential) and the matrix products,
+// which exclude each other: about 7 and 8 ms of N = 65536 with both sides.
 template <int P>
 __global__ __launch_bounds__(256, 4) void k_eval_block(double *__restrict__ W, const double *__restrict__ pts, int d,
-                                                       int64_t p0, int64_t n, int64_t sub0, KParams kp, StageTab T)
+                                                       int64_t p0, int64_t n, int64_t sub0, KParams kp, StageTab T, bool both)
 {
     __shared__ double tile[kBlk * kBlkX];
     const int64_t rs = sub0 + blockIdx.y, cs = blockIdx.x;
@@ -254,9 +258,25 @@ __global__ __launch_bounds__(256, 4) void k_eval_block(double *__restrict__ W, c
         }
     }
     subtree_transform<2, true>(T, cs, tile, kBlkX, nr, false);
-    subtree_transform<2, false>(T, rs, tile, kBlkX, nc, false);
+    if (both) subtree_transform<2, false>(T, rs, tile, kBlkX, nc, false);
     for (int r = wave; r < nr; r += 4)
         if (lane < nc) W[(r0 - p0 + r) * n + c0 + lane] = tile[r * kBlkX + lane];
+}
+
+// Row transform of stage 1 in place: the rows of subtree sub0 + blockIdx.y, 64 columns.
+__global__ __launch_bounds__(256, 4) void k_rows_block(double *__restrict__ W, int64_t p0, int64_t n, int64_t sub0, StageTab T)
+{
+    __shared__ double tile[kBlk * kBlkX];
+    const int64_t rs = sub0 + blockIdx.y, r0 = T.in_pos[T.in_off[rs]], c0 = (int64_t)blockIdx.x * kBlk;
+    const int nr = (int)(T.in_off[rs + 1] - T.in_off[rs]), nc = (int)min<int64_t>(kBlk, n - c0);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double *const P = W + (r0 - p0) * n + c0;
+#pragma unroll 8
+    for (int r = wave; r < nr; r += 4)
+        if (lane < nc) tile[r * kBlkX + lane] = P[r * n + lane];
+    subtree_transform<2, false>(T, rs, tile, kBlkX, nc, false);
+    for (int r = wave; r < nr; r += 4)
+        if (lane < nc) P[r * n + lane] = tile[r * kBlkX + lane];
 }
 
 // Column transform of one later stage on 16 rows of W, in place: subtree sub0 + blockIdx.x.
@@ -884,15 +904,19 @@ extern "C" int spm_kernel_compress(spm_pattern p, spm_tree t, int32_t mp, double
         }
         const int64_t p0 = t->pstart[P.root], rows = t->psize[P.root];
         const dim3 ge((unsigned)stages[0].count, (unsigned)P.nsub);
+        const bool both = stages.size() == 1;
         switch (mp) {
-        case 0: hipLaunchKernelGGL(k_eval_block<0>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T); break;
-        case 1: hipLaunchKernelGGL(k_eval_block<1>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T); break;
-        case 2: hipLaunchKernelGGL(k_eval_block<2>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T); break;
-        default: hipLaunchKernelGGL(k_eval_block<3>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T); break;
+        case 0: hipLaunchKernelGGL(k_eval_block<0>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T, both); break;
+        case 1: hipLaunchKernelGGL(k_eval_block<1>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T, both); break;
+        case 2: hipLaunchKernelGGL(k_eval_block<2>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T, both); break;
+        default: hipLaunchKernelGGL(k_eval_block<3>, ge, dim3(256), 0, s, W.p, D->pts, d, p0, n, P.sub0, kp, D->T, both); break;
         }
         for (size_t j = 1; j < stages.size(); ++j)
             hipLaunchKernelGGL(k_cols_stage, dim3((unsigned)stages[j].count, (unsigned)((rows + 15) / 16)), dim3(kStageT),
                                16 * (stages[j].max_in + kPad) * sizeof(double), s, W.p, rows, n, stages[j].sub0, D->T);
+        if (!both)
+            hipLaunchKernelGGL(k_rows_block, dim3((unsigned)((n + kBlk - 1) / kBlk), (unsigned)P.nsub), dim3(256), 0, s, W.p,
+                               p0, n, P.sub0, D->T);
         if (!P.lv.empty()) {
             if (P.rows_in <= kRowR)
                 hipLaunchKernelGGL(k_rows_panel, dim3((unsigned)((n + kRowC - 1) / kRowC)), dim3(256),

@@ -609,12 +609,10 @@ __device__ inline T load_at(uint64_t adr, int64_t i)
     return ((const __attribute__((address_space(1))) T *)adr)[i];
 }
 
-template <int WAVES>
 __device__ inline void unit_sync()
 {
     __builtin_amdgcn_s_waitcnt(0);
-    if (WAVES > 1) __syncthreads();
-    else __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __syncthreads();
 }
 
 template <int WIDTH>
@@ -669,7 +667,6 @@ __device__ inline void gather_panel(const KTab *T, int slot_base, const double *
         const GatherLane g = gl[0];
         const int kstep = 1 << (LD - lx);
         const char *trow = reinterpret_cast<const char *>(&T->kofs[dl >> lx][slot_base + g.slot]);
-        const int rstride = kstep * 64 * WAVES;   // bytes between the records of consecutive instructions
         for (int ins = wave; ins < nins; ins += 4 * WAVES) {
             // four record reads in flight before the gathers that use them
             int64_t o[4];
@@ -685,7 +682,6 @@ __device__ inline void gather_panel(const KTab *T, int slot_base, const double *
                 lds_gather<WIDTH>(src, half, panel + (ins + q * WAVES) * D);
             }
         }
-        (void)rstride;
     } else if constexpr (WIDTH != 16) {
         // D < X: variant v = ins % nv covers rows [v*D, v*D + D), k = ins / nv
         const int lnv = lx - LD, nv = 1 << lnv;
@@ -873,7 +869,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
     int np3 = np_of(fbe);
     load_entry(fb_of(fbe), np3, e);                // stage 3
     load_bounds(4, fbe);                           // stage 4
-    unit_sync<WAVES>();
+    unit_sync();
     int ks_next = ktab[0].ks, act_next = ktab[0].act;
     if (nst > 0) {
         gather_panel<WAVES, WIDTH>(&ktab[0], 0, A, lds, ks_next, g.lxa, wave, dl, half, gla, zero);
@@ -884,7 +880,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
     // of stage s+1 are issued, then the MFMAs of stage s run.  Nothing issued in an
     // iteration is consumed before the sync that opens the next one.
     for (int s = 0; s < nst; ++s) {
-        unit_sync<WAVES>();                         // gathers of stage s landed; MFMAs of s-1 done
+        unit_sync();                         // gathers of stage s landed; MFMAs of s-1 done
         const int ks_s = ks_next, act_s = act_next;
         const int np4 = np_of(fbe);
         const int32_t fb4 = fb_of(fbe);
@@ -904,7 +900,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
         }
         if (active) {
             const double *sA = lds + (s & 1) * pd, *sB = sA + kKS * Xa;
-            if constexpr (WAVES <= 2 || MR * MC <= 2 || MR + MC >= 8) {
+            if constexpr (MR * MC <= 2 || MR + MC >= 8) {
                 // the fragments of all (up to 8) k steps of the stage are read first, then
                 // the MFMAs issue back to back (patches of 16 or fewer fragment registers
                 // per k step; the wide 1 x 7 patches run at one workgroup per CU and have
@@ -961,7 +957,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
         }
     }
     if (nsplit > 1) {                               // add the k slices in a fixed order
-        unit_sync<WAVES>();
+        unit_sync();
         // waves nw.. hold the partial sums of k slices 1..nsplit-1: slot (wave - nw)
         if (active && kslice > 0)
 #pragma unroll
@@ -970,7 +966,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
                 for (int j = 0; j < MC; ++j)
                     for (int r = 0; r < 4; ++r)
                         lds[((((wave - nw) * MR + i) * MC + j) * 4 + r) * 64 + lane] = acc[i][j][r];
-        unit_sync<WAVES>();
+        unit_sync();
         if (active && kslice == 0)
             for (int sl = 1; sl < nsplit; ++sl) {
                 const int w2 = sl * nw + wave;
@@ -1016,25 +1012,15 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
     }
 }
 
-// Thin units (one side a single 16-row block, at most 7 blocks): no LDS panels.
-// Wave b < nblk owns output block b and loads its MFMA fragments straight from the tile
-// layout into registers, one stage ahead (two register sets, the loop unrolled by two
-// so that the sets are static); the last wave keeps the stage records in a ring of
-// three LDS slots, two stages ahead.  Each stage ends with one barrier that waits for
-// LDS only, so fragment loads stay in flight across it.
+// Units with a side of a single 16-row block: no LDS panels.  The consumer waves load their
+// MFMA fragments straight from the tile layout into registers, at the addresses of the
+// stage records, a stage ahead of their use; the last wave keeps the records in a ring in
+// LDS.  Each stage ends with one barrier that waits for LDS only, so fragment loads stay in
+// flight across it.
 __device__ inline void lds_barrier()
 {
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0); vector memory may stay outstanding
     __builtin_amdgcn_s_barrier();
-}
-
-// Exchange of one double between adjacent lanes (2m <-> 2m + 1).
-__device__ inline double swap_adjacent(double x)
-{
-    const long long v = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);           // quad_perm 1,0,3,2
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0xB1, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
 // Record producer of the register-direct kernels (one wave, lane = this lane): keeps the
