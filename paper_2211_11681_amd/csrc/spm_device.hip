@@ -2944,12 +2944,16 @@ __device__ __forceinline__ void spmm_thin(int64_t q, int64_t p1, int nr, int64_t
         const int w = pc_w[q];
         const double *aq = A + pc_off[q], *xq = xc + pc_g[q];
         constexpr int U = 4;                           // chunks of 16 columns in flight
-        double a[U][NG], x[U][XG];
+        double a[U][NG], x[U][XG], e[NG][XG];          // e: the piece's sums, so that the chains stay short
+#pragma unroll
+        for (int m = 0; m < NG; ++m)
+#pragma unroll
+            for (int g = 0; g < XG; ++g) e[m][g] = 0.0;
         auto mfmas = [&](int u) {
 #pragma unroll
             for (int m = 0; m < NG; ++m)
 #pragma unroll
-                for (int g = 0; g < XG; ++g) d[m][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[u][m], x[u][g], d[m][g], 0, 0, 0);
+                for (int g = 0; g < XG; ++g) e[m][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[u][m], x[u][g], e[m][g], 0, 0, 0);
         };
         int j0 = 0;
         for (; j0 + 16 * U <= w; j0 += 16 * U) {
@@ -2977,6 +2981,10 @@ __device__ __forceinline__ void spmm_thin(int64_t q, int64_t p1, int nr, int64_t
 #pragma unroll
             for (int u = 0; u < U; ++u) mfmas(u);
         }
+#pragma unroll
+        for (int m = 0; m < NG; ++m)
+#pragma unroll
+            for (int g = 0; g < XG; ++g) d[m][g] += e[m][g];
     }
     // lane j + 4b + 16i holds row i, column j of block b: add the blocks
 #pragma unroll
