@@ -14,10 +14,11 @@
 // product with Q on the matrix cores.
 //
 // K is processed in panels of rows: the rows of one subtree (points p0 .. p0+rows).
-//   1. W = the panel's kernel values with stage 1 of the transform applied on both sides:
-//      a workgroup evaluates the block of one stage-1 subtree's rows and another's columns
-//      in LDS, transforms its columns and its rows there and writes it once
-//   2. the later stages of the column transform on the scaling columns of W
+//   1. W = the panel's kernel values with stage 1 of the column transform applied: a
+//      workgroup evaluates the block of one stage-1 subtree's rows and another's columns
+//      in LDS, transforms its columns there and writes it once
+//   2. the later stages of the column transform on the scaling columns of W, then stage 1
+//      of the row transform (where the columns have one stage only, it is part of step 1)
 //   3. the panel's upper clusters combine the scaling rows of W, leaves first
 //   4. extract:         samplet rows of the subtree's clusters -> tiles on S
 //   5. the subtree root's scaling rows move to a buffer U
