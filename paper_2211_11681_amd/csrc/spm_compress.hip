@@ -139,12 +139,13 @@ __device__ __forceinline__ void cluster_task(double *tile, int X, int r0, int li
         run[b] = rp[b] + (loc.base0 + lk) * si;
     }
     auto step = [&](int t, const double (&ft)[KB]) {
-        // the last step's rows past m repeat the last input (its coefficients there are 0)
+        // the last step's rows past m are zeros, as their coefficients are (0 x inf is none)
         const bool whole = RUN && 4 * t + 3 < m;
         const int li = whole ? 0 : loc(min(4 * t + lk, m - 1)) * si;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const double in = whole ? run[b][4 * t * si] : rp[b][li];
+            double in = whole ? run[b][4 * t * si] : rp[b][li];
+            if (4 * t + 3 >= m && 4 * t + lk >= m) in = 0.0;
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
                 if (16 * kb < m)

@@ -1,0 +1,39 @@
+"""The samplet transform at the edges of what it takes: infinities.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def S():
+    from paper_2211_11681_amd import spm
+    spm._lib.load()
+    assert torch.cuda.is_available()
+    return spm
+
+
+@pytest.mark.parametrize("inverse", [False, True])
+@pytest.mark.parametrize("leaf", [16, 17, 18, 19, 33])
+def test_transform_of_an_infinity(S, leaf, inverse):
+    # an infinity in a leaf's last input gives infinities of the unit vector's signs there,
+    # not the NaN of an infinity times a padding zero
+    t = S.Tree(synth.workload_points("cube2", 16 * leaf, 5), leaf, 1)
+    arr = t.arrays()
+    leaf_c = np.nonzero(arr["level"] == t.depth)[0][5]
+    assert arr["pt_size"][leaf_c] == leaf
+    pts = arr["perm"][arr["pt_start"][leaf_c]:arr["pt_start"][leaf_c] + leaf]
+    fun = np.arange(arr["cluster_start"][leaf_c], arr["cluster_start"][leaf_c + 1])
+    src, dst = (fun, pts) if inverse else (pts, fun)
+    x = torch.zeros(3, t.n, dtype=torch.float64, device="cuda")
+    x[0, src[-1]], x[1, src[-1]] = 1.0, float("inf")
+    y = S.fst(t, x, inverse=inverse).cpu().numpy()
+    unit = y[0, dst]
+    live = np.abs(unit) > 1e-10
+    assert live.sum() >= len(dst) // 2
+    assert np.array_equal(y[1, dst][live], np.where(unit[live] > 0, np.inf, -np.inf))
+    assert not y[2].any()
