@@ -828,7 +828,8 @@ static int tree_tables(spm_tree t, TreeNeed need, const spm::TreeDevice **out, c
 
 namespace {
 
-// Stream-ordered device memory, freed in stream order.
+// Stream-ordered device memory, freed in stream order.  The pool keeps what is freed until
+// the stream is next synchronised, and no longer.
 struct StreamBuf {
     double *p = nullptr;
     hipStream_t s;
@@ -839,7 +840,26 @@ struct StreamBuf {
         p = nullptr;
         return false;
     }
-    ~StreamBuf() { if (p) (void)hipFreeAsync(p, s); }
+    void free()
+    {
+        if (p) (void)hipFreeAsync(p, s);
+        p = nullptr;
+    }
+    ~StreamBuf() { free(); }
+};
+
+// The panel buffers of a construction: however it ends, they have been given back when it returns.
+struct PanelBufs {
+    hipStream_t s;
+    StreamBuf W, U;
+    explicit PanelBufs(hipStream_t st) : s(st), W(st), U(st) {}
+    hipError_t finish()
+    {
+        W.free();
+        U.free();
+        return hipStreamSynchronize(s);
+    }
+    ~PanelBufs() { if (W.p || U.p) (void)finish(); }
 };
 
 }  // namespace
@@ -873,7 +893,8 @@ extern "C" int spm_kernel_compress(spm_pattern p, spm_tree t, int32_t mp, double
     const spm::TreeDevice *D;
     int st;
     if ((st = tree_tables(t, TREE_PANELS, &D, "spm_kernel_compress"))) return st;
-    StreamBuf W(s), U(s);
+    PanelBufs bufs(s);
+    StreamBuf &W = bufs.W, &U = bufs.U;
     if (!W.get((size_t)D->maxrows * n * sizeof(double))) return fail(SPM_ENOMEM, "spm_kernel_compress: panel buffer");
     if (D->nu > 0 && !U.get((size_t)D->nu * n * sizeof(double))) return fail(SPM_ENOMEM, "spm_kernel_compress: upper buffer");
     if ((st = allow_lds((const void *)k_rows_panel))) return st;
@@ -939,7 +960,7 @@ extern "C" int spm_kernel_compress(spm_pattern p, spm_tree t, int32_t mp, double
         SPM_HIP(hipGetLastError());
         if ((st = extract(U.p, 0, D->lvl_up[i].first, D->lvl_up[i].second, D->urloff, D->urows))) return st;
     }
-    SPM_HIP(hipStreamSynchronize(s));
+    SPM_HIP(bufs.finish());
     return SPM_OK;
 }
 
