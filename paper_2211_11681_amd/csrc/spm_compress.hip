@@ -30,6 +30,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <new>
@@ -104,6 +105,22 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // index lists the transforms of a kernel block took 229 us per panel of N = 65536, against
 // 60 us of MFMAs.)
 __host__ __device__ inline int64_t frag_index(int m, int kb, int t) { return ((int64_t)kb * ((m + 3) >> 2) + t) * 64; }
+
+// The fragments of cluster blockIdx.x, at foff: M = Q^T (Q column-major, so M[k][i] = q[k m + i]),
+// or the inverse transform's Q.  Formed here, as on the host they took most of a tree's first
+// transform (N = 60000: 15.6 ms, of which the first transform's own work is 0.03 ms).
+__global__ void k_fragments(const int32_t *__restrict__ nin, const int64_t *__restrict__ qoff,
+                            const int64_t *__restrict__ foff, const double *__restrict__ qmat, double *__restrict__ f,
+                            bool inv)
+{
+    const int c = blockIdx.x, m = nin[c], nt = (m + 3) >> 2;
+    const double *q = qmat + qoff[c];
+    double *o = f + foff[c];
+    for (int e = threadIdx.x; e < (m + 15) / 16 * nt * 64; e += blockDim.x) {
+        const int l = e & 63, b = e >> 6, k = 16 * (b / nt) + l % 16, i = 4 * (b % nt) + l / 16;
+        o[e] = k < m && i < m ? (inv ? q[i * m + k] : q[k * m + i]) : 0.0;
+    }
+}
 
 // One cluster's transform of NB blocks of 16 rows (columns) of a tile of row stride X, in
 // place, by one wave: all results (up to NT k steps of four inputs, as many outputs) are
@@ -454,31 +471,47 @@ int allow_lds(const void *k)
     return SPM_OK;
 }
 
-// Host tables collected into one device block.
+// Tables in one device block: host vectors (which stay as they are until the upload), the
+// small ones collected into one copy, and space for what the device fills itself.
 struct Uploader {
-    std::vector<char> host;
-    std::vector<std::pair<void **, size_t>> where;   // device pointer to set, offset
+    struct Part {
+        void **dst;                                    // device pointer to set
+        const void *src;                               // host data, or null
+        size_t bytes, off;
+    };
+    std::vector<Part> parts;
     template <typename T>
-    void add(const T *&dst, const std::vector<T> &v)
-    {
-        host.resize((host.size() + 255) & ~(size_t)255);
-        where.push_back({(void **)&dst, host.size()});
-        const char *p = reinterpret_cast<const char *>(v.data());
-        host.insert(host.end(), p, p + v.size() * sizeof(T));
-    }
+    void add(const T *&dst, const std::vector<T> &v) { parts.push_back({(void **)&dst, v.data(), v.size() * sizeof(T), 0}); }
+    template <typename T>
+    void space(const T *&dst, int64_t n) { parts.push_back({(void **)&dst, nullptr, (size_t)n * sizeof(T), 0}); }
     int upload(void *&block, const char *name)
     {
-        if (hipMalloc(&block, std::max<size_t>(256, host.size())) != hipSuccess) {
+        constexpr size_t kSmall = 64 * 1024;
+        std::stable_partition(parts.begin(), parts.end(), [](const Part &p) { return p.src && p.bytes <= kSmall; });
+        size_t total = 0;
+        std::vector<char> small;
+        for (Part &p : parts) {
+            p.off = total;
+            total += (p.bytes + 255) & ~(size_t)255;
+            if (p.src && p.bytes <= kSmall) {
+                small.resize(total);
+                if (p.bytes) std::memcpy(small.data() + p.off, p.src, p.bytes);
+            }
+        }
+        if (hipMalloc(&block, std::max<size_t>(256, total)) != hipSuccess) {
             block = nullptr;
             return fail(SPM_ENOMEM, std::string(name) + ": device tables");
         }
-        const hipError_t e = hipMemcpy(block, host.data(), host.size(), hipMemcpyHostToDevice);
+        char *const d = static_cast<char *>(block);
+        hipError_t e = small.empty() ? hipSuccess : hipMemcpy(d, small.data(), small.size(), hipMemcpyHostToDevice);
+        for (const Part &p : parts)
+            if (e == hipSuccess && p.src && p.bytes > kSmall) e = hipMemcpy(d + p.off, p.src, p.bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipFree(block);
             block = nullptr;
             return fail(SPM_EHIP, std::string(name) + ": copy of the device tables failed");
         }
-        for (auto [d, off] : where) *d = static_cast<char *>(block) + off;
+        for (const Part &p : parts) *p.dst = d + p.off;
         return SPM_OK;
     }
 };
@@ -504,9 +537,10 @@ struct SubTables {
             lev = t->level[c];
             const int m = t->nin[c];
             auto at = [&](int k) { return index_of[t->slots[t->slotoff[c] + k]]; };
-            ClusterRec R{foff[c], m, std::min(m, 1), m > 0 ? at(0) : 0, 0};
-            while (R.n0 < m && at(R.n0) == at(R.n0 - 1) + 1) ++R.n0;
-            R.base1 = R.n0 < m ? at(R.n0) : 0;
+            const int first = t->son0[c] < 0 ? m : t->nscal[t->son0[c]];   // inputs of the first run
+            ClusterRec R{foff[c], m, first, m > 0 ? at(0) : 0, first < m ? at(first) : 0};
+            if (first > 0 && R.base1 == R.base0 + first) R.n0 = m;         // the second continues it
+            if (first == 0) R = {foff[c], m, m, R.base1, 0};
             rec.push_back(R);
         }
         lv_start.push_back((int64_t)rec.size());
@@ -531,10 +565,10 @@ struct spm::TreeDevice {
     void *block = nullptr, *iblock = nullptr, *pblock = nullptr;
     // stages
     StageTab T{}, TP{};
-    const double *q = nullptr, *finv = nullptr;                     // fragments of the inverse transforms
+    const double *q = nullptr, *finv = nullptr;        // matrices; fragments of the inverse transforms
     std::vector<int64_t> foff;
-    const int64_t *out_pos = nullptr, *sob = nullptr, *perm = nullptr, *slots = nullptr, *qoff = nullptr, *sloff = nullptr;
-    const int32_t *kb = nullptr, *nin = nullptr;
+    const int64_t *out_pos = nullptr, *perm = nullptr, *qoff = nullptr, *d_foff = nullptr;   // d_foff: foff on the device
+    const int32_t *nin = nullptr;
     struct Stage {
         int64_t sub0, count;
         int max_in;
@@ -543,7 +577,8 @@ struct spm::TreeDevice {
     std::vector<int32_t> sub_root;                    // root cluster of every subtree
     // panels
     const double *pts = nullptr;
-    const int32_t *clist = nullptr;
+    const int64_t *sob = nullptr, *slots = nullptr, *sloff = nullptr;
+    const int32_t *clist = nullptr, *kb = nullptr;
     const int64_t *urloff = nullptr, *urows = nullptr;
     struct Panel {
         int32_t root;
@@ -566,7 +601,7 @@ struct spm::TreeDevice {
     int need_stages(const spm_tree_s *t, const char *name);
     int need_inverse(const spm_tree_s *t, const char *name);
     int need_panels(const spm_tree_s *t, const char *name);
-    std::vector<double> fragments(const spm_tree_s *t, bool inv) const;
+    int fragments(const spm_tree_s *t, const double *f, bool inv, const char *name) const;
 };
 
 spm::TreeTables::~TreeTables()
@@ -574,32 +609,22 @@ spm::TreeTables::~TreeTables()
     for (auto &e : by_device) delete e.second;
 }
 
-// Fragments of every cluster's M = Q^T (Q column-major, so M[k][i] = q[k m + i]) or of its
-// inverse Q.
-std::vector<double> spm::TreeDevice::fragments(const spm_tree_s *t, bool inv) const
+// Fills f with the fragments of every cluster (k_fragments), complete on return.
+int spm::TreeDevice::fragments(const spm_tree_s *t, const double *f, bool inv, const char *name) const
 {
-    std::vector<double> v(foff.back(), 0.0);
-    for (int c = 0; c < t->nc; ++c) {
-        const int m = t->nin[c];
-        const double *q = t->qmat.data() + t->qoff[c];
-        for (int kb = 0; 16 * kb < m; ++kb)
-            for (int s = 0; 4 * s < m; ++s)
-                for (int l = 0; l < 64; ++l) {
-                    const int k = 16 * kb + l % 16, i = 4 * s + l / 16;
-                    if (k < m && i < m)
-                        v[foff[c] + frag_index(m, kb, s) + l] = inv ? q[(int64_t)i * m + k] : q[(int64_t)k * m + i];
-                }
-    }
-    return v;
+    hipLaunchKernelGGL(k_fragments, dim3((unsigned)t->nc), dim3(256), 0, nullptr, nin, qoff, d_foff, q, const_cast<double *>(f), inv);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
+        return fail(SPM_EHIP, std::string(name) + ": the device tables could not be formed");
+    return SPM_OK;
 }
 
 int spm::TreeDevice::need_inverse(const spm_tree_s *t, const char *name)
 {
     if (have_inverse) return SPM_OK;
-    const std::vector<double> fi = fragments(t, true);
     Uploader up;
-    up.add(finv, fi);
-    const int rc = up.upload(iblock, name);
+    up.space(finv, foff.back());
+    int rc = iblock ? SPM_OK : up.upload(iblock, name);
+    if (rc == SPM_OK) rc = fragments(t, finv, true, name);
     have_inverse = rc == SPM_OK;
     return rc;
 }
@@ -612,20 +637,25 @@ int spm::TreeDevice::need_stages(const spm_tree_s *t, const char *name)
     foff.assign(nc + 1, 0);
     for (int c = 0; c < nc; ++c) foff[c + 1] = foff[c] + frag_index(t->nin[c], (t->nin[c] + 15) / 16, 0);
     SubTables st(foff);
-    std::vector<int32_t> index_of(n), kbv(nc);
-    for (int c = 0; c < nc; ++c) kbv[c] = c == 0 ? 0 : t->nscal[c];
-    std::vector<int64_t> sobv(n), bos(n);              // basis index <-> slot of its coefficient
-    for (int c = 0; c < nc; ++c)
-        for (int k = kbv[c]; k < t->nin[c]; ++k) {
-            const int64_t b = t->cstart[c] + (k - kbv[c]), sl = t->slots[t->slotoff[c] + k];
-            sobv[b] = sl;
-            bos[sl] = b;
-        }
+    std::vector<int32_t> index_of(n);
+    std::vector<int64_t> bos(n);                       // basis index of the coefficient in a slot
+    for (int c = 0; c < nc; ++c) {
+        const int k0 = c == 0 ? 0 : t->nscal[c];
+        for (int k = k0; k < t->nin[c]; ++k) bos[t->slots[t->slotoff[c] + k]] = t->cstart[c] + (k - k0);
+    }
+    st.rec.reserve(nc);
+    st.in_pos.reserve(n + n / 2);
     stages.clear();
     sub_root.clear();
     std::vector<char> covered(nc, 0);                  // in a subtree of an earlier stage
-    std::vector<int64_t> outv;
-    std::vector<int64_t> width(nc);
+    std::vector<int64_t> outv, width(nc);
+    outv.reserve(n + n / 2);
+    std::vector<int32_t> members;
+    std::vector<int64_t> inputs;
+    auto hand_over = [&](int c, int k) {               // the first k inputs of c become inputs of the subtree
+        const int64_t *sl = t->slots.data() + t->slotoff[c];
+        inputs.insert(inputs.end(), sl, sl + k);
+    };
     for (bool done = false; !done;) {
         const bool first = stages.empty();
         // inputs of the subtree rooted at c: its points, or its topmost covered clusters'
@@ -643,19 +673,19 @@ int spm::TreeDevice::need_stages(const spm_tree_s *t, const char *name)
             stack.push_back(t->son0[c]);
         }
         for (int32_t root : roots) {
-            std::vector<int32_t> members;
-            std::vector<int64_t> inputs;
+            members.clear();
+            inputs.clear();
             stack.assign(1, root);
             while (!stack.empty()) {
                 const int c = stack.back();
                 stack.pop_back();
                 if (covered[c]) {                      // its scaling coefficients
-                    for (int k = 0; k < t->nscal[c]; ++k) inputs.push_back(t->slots[t->slotoff[c] + k]);
+                    hand_over(c, t->nscal[c]);
                     continue;
                 }
                 members.push_back(c);
                 if (t->son0[c] >= 0) { stack.push_back(t->son1[c]); stack.push_back(t->son0[c]); }
-                else for (int k = 0; k < t->nin[c]; ++k) inputs.push_back(t->slots[t->slotoff[c] + k]);
+                else hand_over(c, t->nin[c]);
             }
             st.add(t, members, inputs, index_of);
             for (int64_t pos : inputs) outv.push_back(bos[pos]);
@@ -679,13 +709,16 @@ int spm::TreeDevice::need_stages(const spm_tree_s *t, const char *name)
         stages.push_back(S);
         done = roots.size() == 1 && roots[0] == 0;
     }
-    const std::vector<double> fv = fragments(t, false);
     Uploader up;
     st.put(up, T);
-    up.add(T.f, fv);
-    up.add(nin, t->nin); up.add(qoff, t->qoff); up.add(sloff, t->slotoff); up.add(q, t->qmat);
-    up.add(out_pos, outv); up.add(sob, sobv); up.add(perm, t->perm); up.add(slots, t->slots); up.add(kb, kbv);
-    const int rc = up.upload(block, name);
+    up.space(T.f, foff.back());
+    up.add(d_foff, foff);
+    up.add(nin, t->nin); up.add(qoff, t->qoff); up.add(q, t->qmat);
+    up.add(out_pos, outv); up.add(perm, t->perm);
+    if (block) (void)hipFree(block);                   // of a call that failed after the copies
+    block = nullptr;
+    int rc = up.upload(block, name);
+    if (rc == SPM_OK) rc = fragments(t, T.f, false, name);
     have_stages = rc == SPM_OK;
     return rc;
 }
@@ -796,9 +829,16 @@ int spm::TreeDevice::need_panels(const spm_tree_s *t, const char *name)
         urloffv[c] = (int64_t)urowsv.size();
         urowsv.insert(urowsv.end(), ul[c].begin(), ul[c].end());
     }
+    std::vector<int32_t> kbv(nc);
+    std::vector<int64_t> sobv(n);                      // slot of a basis function's coefficient
+    for (int c = 0; c < nc; ++c) {
+        kbv[c] = c == 0 ? 0 : t->nscal[c];
+        for (int k = kbv[c]; k < t->nin[c]; ++k) sobv[t->cstart[c] + (k - kbv[c])] = t->slots[t->slotoff[c] + k];
+    }
     TP = T;
     Uploader up;
     pt.put(up, TP);
+    up.add(sob, sobv); up.add(kb, kbv); up.add(sloff, t->slotoff); up.add(slots, t->slots);
     up.add(pts, t->pts); up.add(clist, cl); up.add(urloff, urloffv); up.add(urows, urowsv);
     const int rc = up.upload(pblock, name);
     have_panels = rc == SPM_OK;
