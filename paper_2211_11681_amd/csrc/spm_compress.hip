@@ -559,7 +559,8 @@ struct SubTables {
 
 // One device's copies of a tree's transform tables, kept with the tree (it is immutable):
 // the stages from the first fast samplet transform or construction there, the inverse
-// matrices from the first inverse transform, the panels from the first construction.
+// matrices from the first transform of either direction (later ones allocate no tables),
+// the panels from the first construction.
 struct spm::TreeDevice {
     bool have_stages = false, have_inverse = false, have_panels = false;
     void *block = nullptr, *iblock = nullptr, *pblock = nullptr;
@@ -846,8 +847,8 @@ int spm::TreeDevice::need_panels(const spm_tree_s *t, const char *name)
 }
 
 // The tree's tables on the current device (stages, and the construction's panels or the
-// inverse matrices if asked for), uploaded once with synchronous copies.
-enum TreeNeed { TREE_FORWARD, TREE_INVERSE, TREE_PANELS };
+// transforms' inverse matrices), uploaded once with synchronous copies.
+enum TreeNeed { TREE_TRANSFORM, TREE_PANELS };
 static int tree_tables(spm_tree t, TreeNeed need, const spm::TreeDevice **out, const char *name)
 {
     int dev = 0, st;
@@ -857,7 +858,7 @@ static int tree_tables(spm_tree t, TreeNeed need, const spm::TreeDevice **out, c
         spm::TreeDevice *&D = t->tables.by_device[dev];
         if (!D) D = new spm::TreeDevice;
         if ((st = D->need_stages(t, name))) return st;
-        if (need == TREE_INVERSE && (st = D->need_inverse(t, name))) return st;
+        if (need == TREE_TRANSFORM && (st = D->need_inverse(t, name))) return st;
         if (need == TREE_PANELS && (st = D->need_panels(t, name))) return st;
         *out = D;
     } catch (const std::bad_alloc &) {
@@ -1026,7 +1027,7 @@ extern "C" int spm_fst(spm_tree t, const double *X, int32_t r, double *Y, int32_
     hipStream_t s = (hipStream_t)stream;
     const spm::TreeDevice *D;
     int st;
-    if ((st = tree_tables(t, inverse ? TREE_INVERSE : TREE_FORWARD, &D, "spm_fst"))) return st;
+    if ((st = tree_tables(t, TREE_TRANSFORM, &D, "spm_fst"))) return st;
     StreamBuf W(s);                                    // coefficients between stages, by slot
     if (D->stages.size() > 1 && !W.get((size_t)total * sizeof(double))) return fail(SPM_ENOMEM, "spm_fst: work buffer");
     const int ns = (int)D->stages.size();

@@ -1,4 +1,5 @@
-"""The samplet transform at the edges of what it takes: infinities, a tree's first call.
+"""The samplet transform at the edges of what it takes: infinities, a tree's first call,
+capture of the inverse after a forward transform.
 """
 import time
 
@@ -55,3 +56,21 @@ def test_first_transform_of_a_tree(S):
         torch.cuda.synchronize()
         took.append(time.perf_counter() - start)
     assert min(took) < 5e-3, took
+
+
+def test_inverse_is_capturable_after_a_forward_transform(S):
+    # the first call on a tree uploads its tables; every later one is launches alone
+    n, r = 5000, 3
+    t = S.Tree(synth.workload_points("cube2", n, 12), 32, 2)
+    x = torch.from_numpy(2 * synth.uniform(53, np.arange(r * n)).reshape(r, n) - 1).cuda()
+    y = S.fst(t, x)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        back = S.fst(t, y, inverse=True)
+    for k in range(4):
+        y.copy_(S.fst(t, (k + 1) * x))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(back, S.fst(t, y, inverse=True))
+        assert (back - (k + 1) * x).abs().max().item() <= 1e-11
