@@ -527,8 +527,8 @@ void build_groups(spm_pattern_s *p)
     for (int64_t u = 0; u < nu; ++u) p->pair_off[u + 1] = p->pair_off[u] + cnt[u];
     p->pair_a.resize(p->pair_off[nu]);
     p->pair_b.resize(p->pair_off[nu]);
-    p->pair_a_lv.assign(!p->clevel.empty() ? p->pair_off[nu] : 0, 0);
-    p->pair_b_lv.assign(!p->clevel.empty() ? p->pair_off[nu] : 0, 0);
+    p->pair_a_lv.resize(!p->clevel.empty() ? p->pair_off[nu] : 0);
+    p->pair_b_lv.resize(!p->clevel.empty() ? p->pair_off[nu] : 0);
     // Order of a unit's middle clusters (the sum over mu may run in any order).  Both
     // kernels skip work per stage: the register-direct one a 16-column (or 16-row) block
     // of the wide side none of whose members has a tile in the stage, the staged one a
@@ -541,7 +541,7 @@ void build_groups(spm_pattern_s *p)
     const bool lev = !p->clevel.empty();
     // by_level: inside a key group, level by level (finest first), topped up within a level
     auto reorder = [&](int64_t u, int32_t *pa, int32_t *pb, int64_t np, std::vector<Item> &it,
-                       std::vector<int32_t> &tmp, bool by_level) {
+                       std::vector<int32_t> &tmp, std::vector<int32_t> &old, bool by_level) {
         if (np < 2) return;
         const bool wide_c = p->grp_R[p->unit_gc[u]] > 16, wide_r = p->grp_R[p->unit_gr[u]] > 16;
         it.resize(np);
@@ -575,17 +575,17 @@ void build_groups(spm_pattern_s *p)
             }
             g0 = g1;
         }
-        std::vector<int32_t> na(np), nb(np);
-        for (int64_t q = 0; q < np; ++q) { na[q] = pa[tmp[q]]; nb[q] = pb[tmp[q]]; }
-        std::copy(na.begin(), na.end(), pa);
-        std::copy(nb.begin(), nb.end(), pb);
+        for (int32_t *x : {pa, pb}) {
+            old.assign(x, x + np);
+            for (int64_t q = 0; q < np; ++q) x[q] = old[tmp[q]];
+        }
     };
     {
         std::vector<std::thread> th;
         for (unsigned w = 0; w < nth; ++w)
             th.emplace_back([&, w]() {
                 std::vector<Item> it;
-                std::vector<int32_t> tmp;
+                std::vector<int32_t> tmp, old;
                 for (int64_t u = w; u < nu; u += nth) {
                     int32_t *pa = p->pair_a.data() + p->pair_off[u], *pb = p->pair_b.data() + p->pair_off[u];
                     merge(u, pa, pb);
@@ -593,9 +593,9 @@ void build_groups(spm_pattern_s *p)
                         int32_t *qa = p->pair_a_lv.data() + p->pair_off[u], *qb = p->pair_b_lv.data() + p->pair_off[u];
                         std::copy(pa, pa + cnt[u], qa);
                         std::copy(pb, pb + cnt[u], qb);
-                        reorder(u, qa, qb, cnt[u], it, tmp, true);
+                        reorder(u, qa, qb, cnt[u], it, tmp, old, true);
                     }
-                    reorder(u, pa, pb, cnt[u], it, tmp, false);
+                    reorder(u, pa, pb, cnt[u], it, tmp, old, false);
                 }
             });
         for (auto &x : th) x.join();
@@ -624,8 +624,8 @@ void build_groups(spm_pattern_s *p)
     // With levels a second list of stages (by_level) holds clusters of one level each, for
     // the split-precision product; the FP64 and FP32 stages may span two levels.
     std::vector<int64_t> nst(nu, 0);
-    auto pack_list = [&](int64_t u, int32_t *out, bool by_level) {
-        int64_t ns = 0;
+    auto pack_list = [&](int64_t u, spm::RawVec<int32_t> &out, bool by_level) {
+        const size_t o0 = out.size();
         int kacc = 0, np = 0;
         const int64_t f0 = p->pair_off[u], f1 = p->pair_off[u + 1];
         int lv = -1;
@@ -635,8 +635,7 @@ void build_groups(spm_pattern_s *p)
             const int lf = by_level ? p->clevel[p->gl_mu[pa[f]]] : 0;
             if (np == 0 || kacc + km > 32 || np == 8 || lf != lv) {
                 lv = lf;
-                if (out) out[ns] = (int32_t)(f - f0);
-                ++ns;
+                out.push_back((int32_t)(f - f0));
                 kacc = 0;
                 np = 0;
             }
@@ -647,27 +646,33 @@ void build_groups(spm_pattern_s *p)
         // FP64 and FP32 kernels, two or three for the split-precision ones), so that the
         // loops have a single exit; the extra stages are empty (they start at the end of the
         // list)
-        const int mult = by_level ? 6 : 2;
-        while (ns % mult) {
-            if (out) out[ns] = (int32_t)(f1 - f0);
-            ++ns;
-        }
-        nst[u] = ns;
+        const size_t mult = by_level ? 6 : 2;
+        while ((out.size() - o0) % mult) out.push_back((int32_t)(f1 - f0));
+        nst[u] = (int64_t)(out.size() - o0);
     };
-    auto pack_all = [&](bool by_level, std::vector<int64_t> &off, std::vector<int32_t> &first) {
+    // one pass over the lists, whose sizes are gathered (a pass that counts and one that fills
+    // took twice the time, a quarter of the planning of the N = 100000 square)
+    auto pack_all = [&](bool by_level, std::vector<int64_t> &off, spm::RawVec<int32_t> &first) {
+        std::vector<spm::RawVec<int32_t>> part(nth);
+        std::atomic<bool> ok{true};
         {
             std::vector<std::thread> th;
             for (unsigned w = 0; w < nth; ++w)
-                th.emplace_back([&, w]() { for (int64_t u = w; u < nu; u += nth) pack_list(u, nullptr, by_level); });
+                th.emplace_back([&, w]() {
+                    try { for (int64_t u = w; u < nu; u += nth) pack_list(u, part[w], by_level); }
+                    catch (const std::bad_alloc &) { ok = false; }
+                });
             for (auto &x : th) x.join();
         }
+        if (!ok) throw std::bad_alloc();
         off.assign(nu + 1, 0);
         for (int64_t u = 0; u < nu; ++u) off[u + 1] = off[u] + nst[u];
         first.resize(off[nu]);
         std::vector<std::thread> th;
         for (unsigned w = 0; w < nth; ++w)
             th.emplace_back([&, w]() {
-                for (int64_t u = w; u < nu; u += nth) pack_list(u, first.data() + off[u], by_level);
+                const int32_t *from = part[w].data();
+                for (int64_t u = w; u < nu; from += nst[u], u += nth) std::copy(from, from + nst[u], first.data() + off[u]);
             });
         for (auto &x : th) x.join();
     };

@@ -2,11 +2,14 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
 
 #include <cstdint>
+#include <cstdlib>
 #include <map>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
@@ -42,11 +45,32 @@ int fail(int status, const std::string &msg);   // records msg, returns status
             return ::spm::fail(SPM_EINVAL, std::string(name) + ": pattern not uploaded");   \
     } while (0)
 
-// A vector whose resize leaves the new elements unset (large tables filled by threads).
+// A vector for large tables filled and gathered from by threads: resize leaves the new
+// elements unset, and the memory is of huge pages where the system gives them on request
+// (the first touch of 1 GB in 4 KB pages takes 136 ms of one thread, 51 ms so).
 template <typename T>
 struct RawAlloc : std::allocator<T> {
+    static constexpr size_t kHuge = size_t(2) << 20, kLarge = 8 * kHuge;
     template <typename U>
     struct rebind { using other = RawAlloc<U>; };
+    RawAlloc() = default;
+    template <typename U>
+    RawAlloc(const RawAlloc<U> &) {}
+    T *allocate(size_t n)
+    {
+        if (n > (SIZE_MAX - kHuge) / sizeof(T)) throw std::bad_array_new_length();
+        const size_t bytes = n * sizeof(T);
+        if (bytes < kLarge) return std::allocator<T>::allocate(n);
+        void *p = std::aligned_alloc(kHuge, (bytes + kHuge - 1) / kHuge * kHuge);
+        if (!p) throw std::bad_alloc();
+        (void)madvise(p, bytes, MADV_HUGEPAGE);        // advice: small pages otherwise
+        return static_cast<T *>(p);
+    }
+    void deallocate(T *p, size_t n)
+    {
+        if (n * sizeof(T) < kLarge) std::allocator<T>::deallocate(p, n);
+        else std::free(p);
+    }
     template <typename U, typename... A>
     void construct(U *p, A &&...a)
     {
@@ -123,16 +147,16 @@ struct spm_pattern_s {
     std::vector<int32_t> grp_mem;     // ng x 4 member clusters (-1 pads)
     std::vector<int32_t> grp_s, grp_g, grp_R;   // slot size, member count, rows (multiple of 16)
     std::vector<int64_t> gl_rp;       // ng + 1: union lists U(G) = union of the members' block rows
-    std::vector<int32_t> gl_mu;       // cluster of each union entry
-    std::vector<int32_t> gl_tile;     // entries x 4: tile (member k, mu) or -1
-    std::vector<int32_t> unit_gr, unit_gc, unit_out;   // units; unit_out: units x 16 output tiles or -1
+    spm::RawVec<int32_t> gl_mu;       // cluster of each union entry
+    spm::RawVec<int32_t> gl_tile;     // entries x 4: tile (member k, mu) or -1
+    spm::RawVec<int32_t> unit_gr, unit_gc, unit_out;   // units; unit_out: units x 16 output tiles or -1
     std::vector<int32_t> unit_order;  // unit ids grouped by launch class, costly first
     std::vector<int64_t> pair_off;    // units + 1: offsets of each unit's middle-cluster list
-    std::vector<int32_t> pair_a, pair_b;   // union-list entries of mu in U(G_r) and U(G_c)
-    std::vector<int32_t> gl_nm;       // functions of the cluster of each union entry
-    std::vector<int64_t> gl_offd;            // entries x 4: element offset of tile (member, mu), -1 absent
+    spm::RawVec<int32_t> pair_a, pair_b;   // union-list entries of mu in U(G_r) and U(G_c)
+    spm::RawVec<int32_t> gl_nm;       // functions of the cluster of each union entry
+    spm::RawVec<int64_t> gl_offd;            // entries x 4: element offset of tile (member, mu), -1 absent
     std::vector<int64_t> stage_off;   // units + 1: stages of each unit
-    std::vector<int32_t> stage_first; // first pair of each stage, relative to the unit's pair_off
+    spm::RawVec<int32_t> stage_first; // first pair of each stage, relative to the unit's pair_off
     struct Launch {
         int32_t rb, cb, waves;
         int32_t smax_r, smax_c;   // largest slot of the row / column groups of the class
@@ -147,13 +171,13 @@ struct spm_pattern_s {
     // split-precision product scales its operands per row and level
     std::vector<int32_t> clevel;      // nc, or empty
     int32_t nlev = 0;                 // 1 + largest level (0 without levels)
-    std::vector<int32_t> gl_nml;      // entries: functions | level << 8 of the entry's cluster
-    std::vector<int64_t> gl_offT;     // entries x 4: element offset of tile (mu, member), -1 absent
+    spm::RawVec<int32_t> gl_nml;      // entries: functions | level << 8 of the entry's cluster
+    spm::RawVec<int64_t> gl_offT;     // entries x 4: element offset of tile (mu, member), -1 absent
     // the middle clusters of each unit once more, ordered level by level, and stages of one
     // level each (the split-precision product; the FP64 and FP32 order is kept as it is)
-    std::vector<int32_t> pair_a_lv, pair_b_lv;
+    spm::RawVec<int32_t> pair_a_lv, pair_b_lv;
     std::vector<int64_t> stage_off_lv;    // units + 1
-    std::vector<int32_t> stage_first_lv;  // first pair of each stage (relative to the unit's pair_off)
+    spm::RawVec<int32_t> stage_first_lv;  // first pair of each stage (relative to the unit's pair_off)
     // Quads of the FP64 product: the units of a single block, two row groups by two column
     // groups at a time, over one list of middle clusters (empty above kQuadEntries entries)
     std::vector<int32_t> quad_unit;   // quads x 4: unit of (row group a, column group b) at 2a + b, or -1
@@ -163,7 +187,7 @@ struct spm_pattern_s {
     spm::RawVec<int32_t> quad_stage;  // x 4: first middle cluster; their number | k rows << 8 | groups present << 16;
                                       // bit per k row where a cluster starts; first row taken of the first cluster
     std::vector<int32_t> quad_order;  // launch order
-    std::vector<int64_t> pair_offd;   // x 8: as gl_offd for the union lists of the pairs of row groups
+    spm::RawVec<int64_t> pair_offd;   // x 8: as gl_offd for the union lists of the pairs of row groups
     double padded_macs = 0.0;         // multiply-adds the grouped kernel issues (incl. padding)
     bool all_even = false;            // every cluster owns an even number of functions
     bool all_mult4 = false;           // every cluster owns a multiple of 4 functions
