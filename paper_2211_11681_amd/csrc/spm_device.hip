@@ -2865,8 +2865,8 @@ __global__ __launch_bounds__(WAVES * 64, SHARE ? 4 : 1) void k_mgemm_oz(GroupArg
 //    X at the same columns, four columns of X per MFMA; the blocks' sums are added at the
 //    end.  A load instruction takes 16 cycles of a CU's vector memory path whatever it
 //    carries, so the entries of A per load decide.  A load of X touches four of its columns
-//    in every quad of lanes, though, and with more than 12 columns the plain FMA form (a
-//    quarter of the entries of A per load, lanes along X) is ahead: N = 65536 in 3D,
+//    in every quad of lanes, though, and with more than 10 columns (12 in a long row) the
+//    plain FMA form (a quarter of the entries of A per load, lanes along X) is ahead: N = 65536 in 3D,
 //    5 / 10 / 16 columns 764 / 969 / 1282 us against 911 / 967 / 1073; N = 50000 on the
 //    sphere, 5 / 10 columns 253 / 356 against 580 / 611.
 // Whole steps load at a uniform base plus a constant lane offset, with no vector
@@ -2874,6 +2874,13 @@ __global__ __launch_bounds__(WAVES * 64, SHARE ? 4 : 1) void k_mgemm_oz(GroupArg
 // columns.  Rows past n_nu and columns of X past r repeat the last one; those results are
 // not stored.  Four waves per workgroup, so that three or more workgroups fit on a CU.
 constexpr int kSpmmWaves = 4;
+// With 11 or 12 columns in a pass the FMA form moves more values per second over all rows (by
+// 6 %, N = 50000 cube) but takes a row, one workgroup's serial chain, half as long again (12 ns
+// per column of A), so that a launch lasts as long as the longest row where that is at least a
+// 2^13th of the matrix: such rows keep to the 4 x 4 x 4 form.  12 columns, all rows on the
+// 4 x 4 x 4 form / all on FMAs / by this rule: cube 50000 809 / 764 / 755 us, square 100000
+// 1258 / 1178 / 1152, sphere 60000 465 / 720 / 430, square 30011 307 / 339 / 297.
+constexpr int kLongRowShift = 13;
 
 // load at a uniform base plus a 32-bit byte offset (one VGPR per address)
 __device__ __forceinline__ double ld_off(const double *base, uint32_t byte_off)
@@ -3033,7 +3040,7 @@ __device__ __forceinline__ void spmm_thin(int64_t q, int64_t p1, int nr, int64_t
         }
 }
 
-// 13 to 16 columns of X: four groups of 16 column lanes take four columns of X each, plain
+// 11 (13 in a long row) to 16 columns of X: four groups of 16 column lanes take four columns of X each, plain
 // FMAs.
 template <int MAXR, int CB>
 __device__ __forceinline__ void spmm_thin_fma(int64_t q, int64_t p1, int nr, int64_t n, int r, int cc0,
@@ -3094,7 +3101,7 @@ __device__ __forceinline__ void spmm_thin_fma(int64_t q, int64_t p1, int nr, int
 }
 
 template <int CB>
-__global__ __launch_bounds__(64 * kSpmmWaves, 3) void k_spmm(int32_t nc, int64_t n, int32_t r,
+__global__ __launch_bounds__(64 * kSpmmWaves, 3) void k_spmm(int32_t nc, int64_t n, int32_t r, int64_t long_cols,
                                                           const int64_t *__restrict__ pc_rp,
                                                           const int64_t *__restrict__ pc_off,
                                                           const int64_t *__restrict__ pc_g,
@@ -3111,12 +3118,16 @@ __global__ __launch_bounds__(64 * kSpmmWaves, 3) void k_spmm(int32_t nc, int64_t
     if (nr == 0) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t q0 = pc_rp[c] + wave, p1 = pc_rp[c + 1];
+    auto long_row = [&](int c, int nr) {
+        const int64_t first = pc_rp[c];
+        return p1 > first && pc_off[p1 - 1] - pc_off[first] >= long_cols * nr;
+    };
     for (int cc0 = 0; cc0 < r; cc0 += 16 * CB) {
-        const int xg = (min(16, r - cc0) + 3) / 4;     // groups of four columns of X in this pass
+        const int left = min(16, r - cc0), xg = (left + 3) / 4;   // columns of X in this pass, groups of four
 #define SPM_THIN(XG_)                                                                                        \
         if (nr <= 4) spmm_thin<1, XG_, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave]);      \
         else spmm_thin<2, XG_, CB>(q0, p1, nr, n, r, cc0, pc_off, pc_g, pc_w, A, X, red[wave])
-        if (nr <= 8 && xg < 4) {
+        if (nr <= 8 && (left <= 10 || (left <= 12 && long_row(c, nr)))) {
             if (xg == 1) { SPM_THIN(1); }
             else if (xg == 2) { SPM_THIN(2); }
             else { SPM_THIN(3); }
@@ -4058,7 +4069,7 @@ extern "C" int spm_spmm(spm_pattern p, const double *A, const double *X, int32_t
     hipStream_t s = (hipStream_t)stream;
     const dim3 g((unsigned)p->nc), b(64 * kSpmmWaves);
 // passes of 16 columns of X
-    hipLaunchKernelGGL(k_spmm<1>, g, b, 0, s, p->nc, (int64_t)p->n, r, p->d_pc_rp.ptr, p->d_pc_off.ptr,
+    hipLaunchKernelGGL(k_spmm<1>, g, b, 0, s, p->nc, (int64_t)p->n, r, p->n_stored >> kLongRowShift, p->d_pc_rp.ptr, p->d_pc_off.ptr,
                        p->d_pc_g.ptr, p->d_pc_w.ptr, p->d_nfun.ptr, p->d_cstart.ptr, A, X, Y);
     SPM_HIP(hipGetLastError());
     return SPM_OK;
