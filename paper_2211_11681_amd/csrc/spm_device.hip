@@ -541,7 +541,8 @@ __global__ void k_apply_keep(int64_t ns, int prec, const uint8_t *__restrict__ k
 // holds row 4r + l/16, column l%16).  Panels are double-buffered: the gathers of
 // stage s+1 and the stage records of stage s+2 are in flight while the MFMAs of
 // stage s run; the records are fetched in three dependent steps spread over three
-// stages.  WAVES = 8: big units; WAVES = 1: 16 x 16 units.
+// stages.  Takes the classes with several blocks both ways that k_mgemm_wide does not.
+constexpr int kGrpWaves = 8;
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 __device__ double g_zero_word[2];   // zero-initialised source of padding (16 bytes)
@@ -650,7 +651,7 @@ __device__ inline GatherLane gather_lane(int x, int s, int ng, int n0, int n1, i
 // Gathers one operand panel of a stage: instruction `ins` covers the doubles
 // [D*ins, D*ins + D) of the k-major panel with row stride 2^lx; nv = max(1, 2^lx / D)
 // lane variants.  Every load of the stage goes to LDS directly; nothing waits here.
-template <int WAVES, int WIDTH>
+template <int WIDTH>
 __device__ inline void gather_panel(const KTab *T, int slot_base, const double *__restrict__ M,
                                     double *panel, int ks, int lx, int wave, int dl, int half,
                                     const GatherLane (&gl)[4], const double *zero)
@@ -667,19 +668,19 @@ __device__ inline void gather_panel(const KTab *T, int slot_base, const double *
         const GatherLane g = gl[0];
         const int kstep = 1 << (LD - lx);
         const char *trow = reinterpret_cast<const char *>(&T->kofs[dl >> lx][slot_base + g.slot]);
-        for (int ins = wave; ins < nins; ins += 4 * WAVES) {
+        for (int ins = wave; ins < nins; ins += 4 * kGrpWaves) {
             // four record reads in flight before the gathers that use them
             int64_t o[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int iq = ins + q * WAVES < nins ? ins + q * WAVES : ins;
+                const int iq = ins + q * kGrpWaves < nins ? ins + q * kGrpWaves : ins;
                 o[q] = *reinterpret_cast<const int64_t *>(trow + (size_t)iq * kstep * 64);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (ins + q * WAVES >= nins) break;
+                if (ins + q * kGrpWaves >= nins) break;
                 const double *src = (g.ok && o[q] >= 0) ? M + o[q] + g.i : zero;
-                lds_gather<WIDTH>(src, half, panel + (ins + q * WAVES) * D);
+                lds_gather<WIDTH>(src, half, panel + (ins + q * kGrpWaves) * D);
             }
         }
     } else if constexpr (WIDTH != 16) {
@@ -688,12 +689,9 @@ __device__ inline void gather_panel(const KTab *T, int slot_base, const double *
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             if (v >= nv) break;
-            if (WAVES > 1 && WAVES >= nv && v != (wave & (nv - 1))) continue;
+            if (v != (wave & (nv - 1))) continue;
             const GatherLane g = gl[v];
-            const int step = WAVES > nv ? WAVES : nv;
-            const int first = WAVES >= nv ? wave : v + wave * nv;
-            const int ins_step = WAVES >= nv ? step : WAVES * nv;
-            for (int ins = first; ins < nins; ins += ins_step) {
+            for (int ins = wave; ins < nins; ins += kGrpWaves) {
                 const int kk = ins >> lnv;
                 const int64_t o = T->kofs[kk][slot_base + g.slot];
                 const double *src = (g.ok && o >= 0) ? M + o + g.i : zero;
@@ -703,14 +701,14 @@ __device__ inline void gather_panel(const KTab *T, int slot_base, const double *
     }
 }
 
-template <int WAVES, int WIDTH, int MR, int MC>
-__global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const double *__restrict__ A,
+template <int WIDTH, int MR, int MC>
+__global__ __launch_bounds__(kGrpWaves * 64) void k_mgemm_grp(GroupArgs g, const double *__restrict__ A,
                                                          const double *__restrict__ B, double *__restrict__ C)
 {
     extern __shared__ double lds[];
     constexpr int D = WIDTH * 8;                   // doubles per gather instruction
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t uidx = blockIdx.x;
     if (uidx >= g.count) return;
     const int Xa = 1 << g.lxa, Xb = 1 << g.lxb;
@@ -762,7 +760,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
     // no stage waits for its own loads.  Lane (p, slot): middle cluster p of the stage,
     // slot 0..3 row members, 4..7 column members; slot 0 also carries the cluster size.
     // the stage records are kept by a wave without MFMA blocks when there is one
-    const int twave = nw * nsplit < WAVES ? WAVES - 1 : 0;
+    const int twave = nw * nsplit < kGrpWaves ? kGrpWaves - 1 : 0;
     const int tp = lane >> 3, tslot = lane & 7, tk = tslot & 3;
     const bool tvalid = tslot < 4 ? tk < ngr : tk < ngc;
     // bounds of a stage: lane 0 loads its first union entry, lane 1 the end (per lane, so
@@ -872,8 +870,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
     unit_sync();
     int ks_next = ktab[0].ks, act_next = ktab[0].act;
     if (nst > 0) {
-        gather_panel<WAVES, WIDTH>(&ktab[0], 0, A, lds, ks_next, g.lxa, wave, dl, half, gla, zero);
-        gather_panel<WAVES, WIDTH>(&ktab[0], 4, B, lds + kKS * Xa, ks_next, g.lxb, wave, dl, half, glb, zero);
+        gather_panel<WIDTH>(&ktab[0], 0, A, lds, ks_next, g.lxa, wave, dl, half, gla, zero);
+        gather_panel<WIDTH>(&ktab[0], 4, B, lds + kKS * Xa, ks_next, g.lxb, wave, dl, half, glb, zero);
     }
     // Iteration s: records s+2 are written into the slot of stage s (whose gathers were
     // issued one iteration earlier), the record loads advance by one stage, the gathers
@@ -895,8 +893,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_grp(GroupArgs g, const dou
             double *buf = lds + ((s + 1) & 1) * pd;
             ks_next = T1->ks;
             act_next = T1->act;
-            gather_panel<WAVES, WIDTH>(T1, 0, A, buf, ks_next, g.lxa, wave, dl, half, gla, zero);
-            gather_panel<WAVES, WIDTH>(T1, 4, B, buf + kKS * Xa, ks_next, g.lxb, wave, dl, half, glb, zero);
+            gather_panel<WIDTH>(T1, 0, A, buf, ks_next, g.lxa, wave, dl, half, gla, zero);
+            gather_panel<WIDTH>(T1, 4, B, buf + kKS * Xa, ks_next, g.lxb, wave, dl, half, glb, zero);
         }
         if (active) {
             const double *sA = lds + (s & 1) * pd, *sB = sA + kKS * Xa;
@@ -2133,7 +2131,7 @@ __global__ __launch_bounds__(512, 4) void k_mgemm_wide(GroupArgs g, const E *__r
 // F32ACC: the same unit schedule with FP32 operands and v_mfma_f32_16x16x4f32.  Each
 // stage's MFMA sums (FP32, 32 k rows) are added into FP64 accumulators; the result is
 // rounded to FP32 once.  Where every cluster size is a multiple of four, units of 5 to 7
-// blocks a side run on k_mgemm_wide and those of one block by 4 to 8 on k_mgemm_f32side;
+// blocks a side run on k_mgemm_wide and those of one block by 4 to 7 on k_mgemm_f32side;
 // the others are register-direct here: consumer wave w owns
 // block row w (all column blocks, MC >= CB) when the unit has several block rows, else
 // column block w; the last wave keeps the records.  QUAD (every cluster size a multiple
@@ -2330,7 +2328,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_mgemm_f32acc(GroupArgs g, const 
     }
 }
 
-// One block on one side, 4 to 8 on the other, every cluster size a multiple of four: a
+// One block on one side, 4 to 7 on the other (a pattern with units of 8 blocks has an 8 x 8
+// class and takes the per-tile kernel), every cluster size a multiple of four: a
 // consumer wave owns 64 positions of the wider side, four adjacent ones a lane, so that one
 // 16-byte load per k step, whose lane quads read 64 bytes of a column, gives the operands
 // of four MFMAs (block c: the positions 4 l + c) with nothing to transpose; the single block
@@ -3165,15 +3164,6 @@ __device__ inline typename BufWord<T>::type buf_load(__amdgpu_buffer_rsrc_t r, i
     else
         return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
-template <typename T>
-__device__ inline void buf_store(__amdgpu_buffer_rsrc_t r, int off, typename BufWord<T>::type v)
-{
-    using u32x2 = __attribute__((ext_vector_type(2))) unsigned;
-    if constexpr (sizeof(T) == 8)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 0);
-    else
-        __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, 0);
-}
 
 // out = the tiles of in, each transposed into the place of its mirror tile.  One
 // wavefront per run of `run` (at most kTrRun) consecutive tiles: lane k loads the descriptors of tile
@@ -3443,7 +3433,7 @@ int launch_gemm_abt(spm_pattern p, const double *A, const double *B, double *C, 
         const void *k = nullptr;
 #define SPM_GRP_PICK(MR_, MC_)                                                                            \
         if (mr == MR_ && mc == MC_)                                                                       \
-            k = wide ? (const void *)k_mgemm_grp<8, 16, MR_, MC_> : (const void *)k_mgemm_grp<8, 4, MR_, MC_>;
+            k = wide ? (const void *)k_mgemm_grp<16, MR_, MC_> : (const void *)k_mgemm_grp<4, MR_, MC_>;
         SPM_GRP_PICK(1, 1) SPM_GRP_PICK(1, 2) SPM_GRP_PICK(2, 1) SPM_GRP_PICK(2, 2)
         SPM_GRP_PICK(1, 4) SPM_GRP_PICK(4, 1) SPM_GRP_PICK(2, 4) SPM_GRP_PICK(4, 2)
         SPM_GRP_PICK(1, 7) SPM_GRP_PICK(7, 1)
