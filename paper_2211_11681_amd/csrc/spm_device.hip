@@ -1711,9 +1711,10 @@ __global__ __launch_bounds__(128, 4) void k_mgemm_quad(GroupArgs g, QuadArgs z, 
 // whichever it is: with shared columns the block is computed transposed.
 //
 // In units of slot 20 (clusters of 17 to 20 functions) a wave's rows are of several members.
-// In a stage that not all of these have, an absent one's zeros must not meet an infinity or
-// a NaN of the shared side: where one is seen in such a stage, the wave's results are formed
-// once more at the end, tile by tile.
+// In a stage that not all of these have, the zeros of an absent one meet the shared side, and
+// an infinity or a NaN there leaves a NaN.  A wave whose sums hold one at the end forms them
+// once more, tile by tile (without a NaN that costs eight comparisons a unit; a test of the
+// shared values in the loop took 1 % of the products of such clusters).
 constexpr int kSideLead = 5;
 constexpr size_t side_lds_bytes() { return ring_bytes<kSideLead>() + (kSideLead + 1) * 4096; }
 
@@ -1753,7 +1754,6 @@ __global__ __launch_bounds__(320, 6) void k_mgemm_side(GroupArgs g, const double
     const uint64_t o0 = 8 * max(0, min(xi, no - (W16 ? 2 : 1))), o1 = 8 * max(0, min(xi + 1, no - 1));
     const int m0 = aligned ? wave : 32 * wave / osz, m1 = aligned ? wave : min((32 * wave + 31) / osz, 3);
     const int omask = (((2 << m1) - 1) & ~((1 << m0) - 1)) << (shA ? 4 : 0);
-    const int all = omask & ((1 << (shA ? un.ngc : un.ngr)) - 1) << (shA ? 4 : 0);
     typedef double dbl2 __attribute__((ext_vector_type(2)));
     // One stage of operands in registers: a k step is computed, then refilled with the same
     // step of the next stage.  (Two stages took 128 registers, which let only two
@@ -1776,7 +1776,6 @@ __global__ __launch_bounds__(320, 6) void k_mgemm_side(GroupArgs g, const double
         load_own(ring[0].adr[oslot][4 * t + lk], qo[t]);
         __builtin_amdgcn_sched_barrier(0);
     }
-    bool redo = false;                                 // a mixed stage had shared values that are not finite
     int slot = 1, shs = 0;                             // ring slots of stages s + 1 and s
     for (int s = 0; s < un.nst; ++s) {
         const double *sp = shr + shs * 512 + lane;
@@ -1791,12 +1790,6 @@ __global__ __launch_bounds__(320, 6) void k_mgemm_side(GroupArgs g, const double
 #pragma unroll
             for (int t = 0; t < 4; ++t) ad[t] = ap[4 * (4 * h + t)];
             __builtin_amdgcn_sched_barrier(0);
-            if (W16 && act != 0 && act != all) {
-                bool odd = false;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) odd |= !(__builtin_fabs(sv[t]) < HUGE_VAL);
-                redo |= __builtin_amdgcn_ballot_w64(odd) != 0;
-            }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 dbl2 &o = qo[4 * h + t];
@@ -1814,7 +1807,10 @@ __global__ __launch_bounds__(320, 6) void k_mgemm_side(GroupArgs g, const double
         lds_barrier();
     }
     // register r: function 4r + lk of the shared side, row x (ax) and x + 1 (ay) of the own side
-    if (W16 && redo) {
+    bool nan = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) nan |= ax[r] != ax[r] || ay[r] != ay[r];
+    if (W16 && !aligned && __builtin_amdgcn_ballot_w64(nan) != 0) {
         const int ssz = shA ? un.sr : un.sc, nmem = shA ? un.ngc : un.ngr;
         const double *const O = shA ? B : A, *const S = shA ? A : B;
 #pragma unroll
