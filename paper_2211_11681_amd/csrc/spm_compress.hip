@@ -1007,8 +1007,8 @@ extern "C" int spm_kernel_compress(spm_pattern p, spm_tree t, int32_t mp, double
 
 // Fast samplet transform of r vectors (Section 3.2): Y = T X with X in the points'
 // original order and Y in basis order, or the inverse X = T^T Y, one launch per stage of
-// the tree (two or three up to a million points; one per level, plus the permutations, was
-// bound by the launches).
+// the tree (three at 131072 points with four moments, four at a million with six; one per
+// level, plus the permutations, was bound by the launches).
 extern "C" int spm_fst(spm_tree t, const double *X, int32_t r, double *Y, int32_t inverse, void *stream)
 {
     if (!t) return fail(SPM_EINVAL, "spm_fst: null tree");

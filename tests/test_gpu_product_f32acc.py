@@ -1,6 +1,7 @@
 """The FP32-accumulate product on the classes of the kernels that load four rows at a time
-(every cluster size a multiple of four), against the FP64 oracle: one block by 4 to 8, and
-5 to 7 blocks by 5 to 7, both orders, full and masked patterns.  Tolerance 1e-6 as in the
+(every cluster size a multiple of four), against the FP64 oracle: one block by 4 to 7, and
+5 to 7 blocks by 5 to 7, both orders, full and masked patterns; with 8 blocks the product
+runs on the per-tile kernel.  Tolerance 1e-6 as in the
 other FP32 product tests: operands and the sums of 32 k rows are rounded to 2^-24.
 """
 import numpy as np
@@ -30,7 +31,7 @@ CASES = [(72, 36, 5.0, 4),        # two leaves of 32 functions
          (24 * 32, 24, 1.0, 5),   # 20 each: members end inside a block and inside a wave's 64 rows
          (28 * 32, 28, 1.0, 6),   # 24
          (32 * 32, 32, 0.6, 7),   # 28
-         (36 * 16, 36, 1.0, 8)]   # 32: side kernel only
+         (36 * 16, 36, 1.0, 8)]   # 32: per-tile kernel
 
 
 @pytest.mark.parametrize("masked", [False, True])

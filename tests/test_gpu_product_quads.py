@@ -1,6 +1,6 @@
 """The masked product over patterns with enough one-block units for the two-by-two kernel
 (4096 pairs of row group pairs), against the FP64 oracle: clusters of 0 to 9 functions, so
-that the 16 k rows of a stage cut clusters, hold eight small ones or one kind of them only,
+that the 32 k rows of a stage cut clusters, hold eight small ones or one kind of them only,
 odd numbers of groups, masked positions.  Tolerance 1e-12 as in the other product tests (a
 sum of at most N terms).
 """

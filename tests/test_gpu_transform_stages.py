@@ -1,5 +1,5 @@
 """The staged samplet transform and the construction of K^eta where their stages can go wrong:
-one to four stages, clusters with more than 32 inputs, leaves smaller than the number of
+one to three stages, clusters with more than 32 inputs, leaves smaller than the number of
 moments (their functions are all handed up, so a cluster's inputs are not two runs), sizes
 of a block's edge, ragged clusters, single and many vectors.  Against the oracle: the
 transform to 1e-13 of the vector norm (log N orthogonal steps of at most 64 terms each),
