@@ -39,7 +39,7 @@ void for_each_table(spm_pattern_s *p, F &&f)
     f(p->d_grp_mem, p->grp_mem); f(p->d_grp_s, p->grp_s); f(p->d_grp_g, p->grp_g); f(p->d_grp_R, p->grp_R);
     f(p->d_gl_rp, p->gl_rp); f(p->d_gl_mu, p->gl_mu); f(p->d_gl_tile, p->gl_tile);
     f(p->d_unit_gr, p->unit_gr); f(p->d_unit_gc, p->unit_gc); f(p->d_unit_out, p->unit_out);
-    f(p->d_unit_order, p->unit_order); f(p->d_pair_off, p->pair_off); f(p->d_pair_a, p->pair_a);
+    f(p->d_unit_order, p->unit_order); f(p->d_unit_order_lv, p->unit_order_lv); f(p->d_pair_off, p->pair_off); f(p->d_pair_a, p->pair_a);
     f(p->d_pair_b, p->pair_b); f(p->d_gl_nm, p->gl_nm); f(p->d_gl_offd, p->gl_offd);
     f(p->d_stage_off, p->stage_off); f(p->d_stage_first, p->stage_first); f(p->d_csr_pos, p->csr_pos);
     f(p->d_clevel, p->clevel); f(p->d_gl_nml, p->gl_nml); f(p->d_gl_offT, p->gl_offT);
@@ -1081,8 +1081,10 @@ __device__ void record_producer(const GroupArgs &g, const UnitInfo &ui, double *
     // g.gl_nm the cluster size | level << 8 (the caller passes those tables)
     constexpr bool OZ = std::is_same<Rec, OzTab>::value;
     // ahead of the consumer waves of its SIMD: every vector instruction would else wait for
-    // their MFMAs, which hold the vector unit for 64 cycles each
-    __builtin_amdgcn_s_setprio(3);
+    // their MFMAs, which hold the vector unit for 64 cycles each (the bf16 ones of the
+    // split-precision product's one-block units are short: 72.4 against 70.7 ms there with it,
+    // cube of clusters of 4 to 12 functions, N = 32768)
+    if constexpr (!OZ || SHARE) __builtin_amdgcn_s_setprio(3);
     const int64_t s0 = ui.s0, p0 = ui.p0;
     const int nst = ui.nst, npairs = ui.npairs, ngr = ui.ngr, ngc = ui.ngc;
     const int nr0 = ui.nr0, nr1 = ui.nr1, nr2 = ui.nr2, nr3 = ui.nr3;
@@ -3592,7 +3594,9 @@ int gemm_oz_ws(spm_pattern p, const float *A, int ta, const float *B, int tb, fl
     int dev = 0;
     SPM_HIP(hipGetDevice(&dev));
     for (const auto &L : p->launches) {
-        g.first = L.first;
+        const bool own_order = L.rb * L.cb == 1;           // its own list of the (1, 1) class
+        g.unit_order = own_order ? p->d_unit_order_lv.ptr : p->d_unit_order.ptr;
+        g.first = own_order ? 0 : L.first;
         g.count = L.count;
         g.RB = L.rb;
         g.CB = L.cb;

@@ -691,8 +691,10 @@ void build_groups(spm_pattern_s *p)
     // strips are bands of kBand row groups, walked column group by column group, so that
     // the units that read one column panel start together and find it in L2 (FP64 product,
     // N = 131072 square: 122.9 ms with single rows, 119.2 / 118.5 / 117.4 / 130.7 ms with
-    // bands of 2 / 4 / 8 / 16; N = 65536 cube: 123.3, 122.5 / 122.1 / 122.9 / 130.8 ms).  Workgroups are dispatched to the 8 XCDs round robin,
-    // so the launch order interleaves the eight per-XCD lists.
+    // bands of 2 / 4 / 8 / 16; N = 65536 cube: 123.3, 122.5 / 122.1 / 122.9 / 130.8 ms).  The
+    // split-precision product is faster with strips of one row group there too (cube of
+    // clusters of 4 to 12 functions, N = 32768: 70.9 ms, 74.1 in bands).  Workgroups are dispatched to the 8 XCDs round robin, so the launch order
+    // interleaves the eight per-XCD lists.
     auto key = [&](int64_t u) { return p->grp_R[p->unit_gr[u]] / 16 * 16 + p->grp_R[p->unit_gc[u]] / 16; };
     std::vector<int64_t> idx(nu);
     for (int64_t u = 0; u < nu; ++u) idx[u] = u;
@@ -700,64 +702,67 @@ void build_groups(spm_pattern_s *p)
         const int kx = key(x), ky = key(y);
         return kx != ky ? kx < ky : x < y;
     });
+    // the units idx[c0 .. c1) of one class in launch order; banded: units of a single block in
+    // bands, else in strips of one row group
+    auto order_class = [&](int64_t c0, int64_t c1, bool banded, auto &out) {
+        const int rb = key(idx[c0]) / 16, cb = key(idx[c0]) % 16;
+        constexpr int kBand = 4;
+        std::vector<std::pair<int64_t, int64_t>> bu;       // (strip key, unit)
+        bu.reserve(c1 - c0);
+        for (int64_t i = c0; i < c1; ++i) {
+            const int64_t u = idx[i];
+            bu.push_back({banded ? p->unit_gr[u] / kBand : cb > rb ? p->unit_gc[u] : p->unit_gr[u], u});
+        }
+        std::sort(bu.begin(), bu.end(), [&](const std::pair<int64_t, int64_t> &x, const std::pair<int64_t, int64_t> &y) {
+            if (x.first != y.first) return x.first < y.first;
+            if (banded) {                                  // column group, then row group (units are listed by row)
+                const int32_t gx = p->unit_gc[x.second], gy = p->unit_gc[y.second];
+                return gx != gy ? gx < gy : x.second < y.second;
+            }
+            if (cost[x.second] != cost[y.second]) return cost[x.second] > cost[y.second];
+            return x.second < y.second;
+        });
+        struct Blk { int64_t b0, b1; double w; };
+        std::vector<Blk> blks;
+        for (int64_t i = 0; i < (int64_t)bu.size();) {
+            int64_t j = i;
+            double w = 0.0;
+            while (j < (int64_t)bu.size() && bu[j].first == bu[i].first) w += cost[bu[j++].second];
+            blks.push_back({i, j, w});
+            i = j;
+        }
+        std::stable_sort(blks.begin(), blks.end(), [](const Blk &x, const Blk &y) { return x.w > y.w; });
+        std::vector<std::vector<int64_t>> lists(8);
+        double load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (const auto &B : blks) {
+            int x = 0;
+            for (int y = 1; y < 8; ++y)
+                if (load[y] < load[x]) x = y;
+            load[x] += B.w;
+            for (int64_t i = B.b0; i < B.b1; ++i) lists[x].push_back(bu[i].second);
+        }
+        std::vector<size_t> pos(8, 0);
+        for (int64_t n = c0; n < c1; ++n) {
+            int x = (int)((n - c0) % 8);
+            if (pos[x] >= lists[x].size()) {               // list exhausted: take from the longest remaining one
+                int best = 0;
+                for (int y = 1; y < 8; ++y)
+                    if (lists[y].size() - pos[y] > lists[best].size() - pos[best]) best = y;
+                x = best;
+            }
+            out.push_back(lists[x][pos[x]++]);
+        }
+    };
+    p->unit_order_lv.clear();
     {
         std::vector<int64_t> out;
         out.reserve(nu);
-        int64_t c0 = 0;
-        while (c0 < nu) {
-            int64_t c1 = c0;
+        for (int64_t c0 = 0, c1; c0 < nu; c0 = c1) {
+            c1 = c0;
             while (c1 < nu && key(idx[c1]) == key(idx[c0])) ++c1;
-            const int k = key(idx[c0]);
-            const int rb = k / 16, cb = k % 16;
-            // strips of the class
-            constexpr int kBand = 4;
-            const bool single = rb * cb == 1;
-            std::vector<std::pair<int64_t, int64_t>> bu;   // (strip key, unit)
-            bu.reserve(c1 - c0);
-            for (int64_t i = c0; i < c1; ++i) {
-                const int64_t u = idx[i];
-                bu.push_back({single ? p->unit_gr[u] / kBand : cb > rb ? p->unit_gc[u] : p->unit_gr[u], u});
-            }
-            std::sort(bu.begin(), bu.end(), [&](const std::pair<int64_t, int64_t> &x, const std::pair<int64_t, int64_t> &y) {
-                if (x.first != y.first) return x.first < y.first;
-                if (single) {                              // column group, then row group (units are listed by row)
-                    const int32_t gx = p->unit_gc[x.second], gy = p->unit_gc[y.second];
-                    return gx != gy ? gx < gy : x.second < y.second;
-                }
-                if (cost[x.second] != cost[y.second]) return cost[x.second] > cost[y.second];
-                return x.second < y.second;
-            });
-            struct Blk { int64_t b0, b1; double w; };
-            std::vector<Blk> blks;
-            for (int64_t i = 0; i < (int64_t)bu.size();) {
-                int64_t j = i;
-                double w = 0.0;
-                while (j < (int64_t)bu.size() && bu[j].first == bu[i].first) w += cost[bu[j++].second];
-                blks.push_back({i, j, w});
-                i = j;
-            }
-            std::stable_sort(blks.begin(), blks.end(), [](const Blk &x, const Blk &y) { return x.w > y.w; });
-            std::vector<std::vector<int64_t>> lists(8);
-            double load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (const auto &B : blks) {
-                int x = 0;
-                for (int y = 1; y < 8; ++y)
-                    if (load[y] < load[x]) x = y;
-                load[x] += B.w;
-                for (int64_t i = B.b0; i < B.b1; ++i) lists[x].push_back(bu[i].second);
-            }
-            std::vector<size_t> pos(8, 0);
-            for (int64_t n = c0; n < c1; ++n) {
-                int x = (int)((n - c0) % 8);
-                if (pos[x] >= lists[x].size()) {       // list exhausted: take from the longest remaining one
-                    int best = 0;
-                    for (int y = 1; y < 8; ++y)
-                        if (lists[y].size() - pos[y] > lists[best].size() - pos[best]) best = y;
-                    x = best;
-                }
-                out.push_back(lists[x][pos[x]++]);
-            }
-            c0 = c1;
+            const bool single = key(idx[c0]) == 17;        // one block by one
+            order_class(c0, c1, single, out);
+            if (single && lev && p->all_even) order_class(c0, c1, false, p->unit_order_lv);
         }
         idx.swap(out);
     }

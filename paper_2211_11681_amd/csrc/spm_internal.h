@@ -151,6 +151,7 @@ struct spm_pattern_s {
     spm::RawVec<int32_t> gl_tile;     // entries x 4: tile (member k, mu) or -1
     spm::RawVec<int32_t> unit_gr, unit_gc, unit_out;   // units; unit_out: units x 16 output tiles or -1
     std::vector<int32_t> unit_order;  // unit ids grouped by launch class, costly first
+    std::vector<int32_t> unit_order_lv;   // the (1, 1) class for the split-precision product (with levels, even sizes)
     std::vector<int64_t> pair_off;    // units + 1: offsets of each unit's middle-cluster list
     spm::RawVec<int32_t> pair_a, pair_b;   // union-list entries of mu in U(G_r) and U(G_c)
     spm::RawVec<int32_t> gl_nm;       // functions of the cluster of each union entry
@@ -206,7 +207,7 @@ struct spm_pattern_s {
     spm::DevBuf<int32_t> d_pc_w;
     spm::DevBuf<int32_t> d_nfun, d_tile_row, d_tile_col, d_trans, d_diag_tile, d_order;
     spm::DevBuf<int32_t> d_grp_mem, d_grp_s, d_grp_g, d_grp_R, d_gl_mu, d_gl_tile, d_unit_gr, d_unit_gc, d_unit_out,
-        d_unit_order;
+        d_unit_order, d_unit_order_lv;
     spm::DevBuf<int64_t> d_gl_rp, d_pair_off, d_gl_offd, d_stage_off;
     spm::DevBuf<int32_t> d_pair_a, d_pair_b, d_gl_nm, d_stage_first;
     spm::DevBuf<int32_t> d_clevel, d_gl_nml, d_stage_first_lv, d_pair_a_lv, d_pair_b_lv;
