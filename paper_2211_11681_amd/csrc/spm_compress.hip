@@ -848,17 +848,25 @@ int spm::TreeDevice::need_panels(const spm_tree_s *t, const char *name)
 
 // The tree's tables on the current device (stages, and the construction's panels or the
 // transforms' inverse matrices), uploaded once with synchronous copies.
-enum TreeNeed { TREE_TRANSFORM, TREE_PANELS };
-static int tree_tables(spm_tree t, TreeNeed need, const spm::TreeDevice **out, const char *name)
+enum TreeNeed { TREE_FORWARD, TREE_INVERSE, TREE_PANELS };
+static int tree_tables(spm_tree t, TreeNeed need, hipStream_t s, const spm::TreeDevice **out, const char *name)
 {
     int dev = 0, st;
     SPM_HIP(hipGetDevice(&dev));
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (need == TREE_FORWARD && hipStreamIsCapturing(s, &cap) != hipSuccess) {   // (another stream's, on the null stream)
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusActive;
+    }
     std::lock_guard<std::mutex> lock(t->tables.mu);
     try {
         spm::TreeDevice *&D = t->tables.by_device[dev];
         if (!D) D = new spm::TreeDevice;
         if ((st = D->need_stages(t, name))) return st;
-        if (need == TREE_TRANSFORM && (st = D->need_inverse(t, name))) return st;
+        if (need == TREE_INVERSE && (st = D->need_inverse(t, name))) return st;
+        // a forward transform goes without them where they find no memory or the stream is being
+        // captured (a construction may have left the stages); an inverse tries again
+        if (need == TREE_FORWARD && cap == hipStreamCaptureStatusNone && D->need_inverse(t, name)) (void)hipGetLastError();
         if (need == TREE_PANELS && (st = D->need_panels(t, name))) return st;
         *out = D;
     } catch (const std::bad_alloc &) {
@@ -933,7 +941,7 @@ extern "C" int spm_kernel_compress(spm_pattern p, spm_tree t, int32_t mp, double
 
     const spm::TreeDevice *D;
     int st;
-    if ((st = tree_tables(t, TREE_PANELS, &D, "spm_kernel_compress"))) return st;
+    if ((st = tree_tables(t, TREE_PANELS, s, &D, "spm_kernel_compress"))) return st;
     PanelBufs bufs(s);
     StreamBuf &W = bufs.W, &U = bufs.U;
     if (!W.get((size_t)D->maxrows * n * sizeof(double))) return fail(SPM_ENOMEM, "spm_kernel_compress: panel buffer");
@@ -1027,7 +1035,7 @@ extern "C" int spm_fst(spm_tree t, const double *X, int32_t r, double *Y, int32_
     hipStream_t s = (hipStream_t)stream;
     const spm::TreeDevice *D;
     int st;
-    if ((st = tree_tables(t, TREE_TRANSFORM, &D, "spm_fst"))) return st;
+    if ((st = tree_tables(t, inverse ? TREE_INVERSE : TREE_FORWARD, s, &D, "spm_fst"))) return st;
     StreamBuf W(s);                                    // coefficients between stages, by slot
     if (D->stages.size() > 1 && !W.get((size_t)total * sizeof(double))) return fail(SPM_ENOMEM, "spm_fst: work buffer");
     const int ns = (int)D->stages.size();

@@ -1,5 +1,5 @@
 """The samplet transform at the edges of what it takes: infinities, a tree's first call,
-capture of the inverse after a forward transform.
+capture of a transform after another call on the tree.
 """
 import time
 
@@ -74,3 +74,21 @@ def test_inverse_is_capturable_after_a_forward_transform(S):
         torch.cuda.synchronize()
         assert torch.equal(back, S.fst(t, y, inverse=True))
         assert (back - (k + 1) * x).abs().max().item() <= 1e-11
+
+
+def test_forward_is_capturable_after_a_construction(S):
+    n, r = 2000, 3
+    t = S.Tree(synth.workload_points("cube2", n, 12), 32, 1)
+    pat = S.Pattern.from_tree(t, 1.0)
+    S.kernel_compress(pat, t, 1, 0.3, 1.0 / n)
+    x = torch.from_numpy(2 * synth.uniform(53, np.arange(r * n)).reshape(r, n) - 1).cuda()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = S.fst(t, x)
+    for k in range(4):
+        x.mul_(1.5)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, S.fst(t, x))
+        assert (S.fst(t, y, inverse=True) - x).abs().max().item() <= 1e-11
